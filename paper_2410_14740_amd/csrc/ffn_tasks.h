@@ -1,7 +1,7 @@
 // Task geometry of the one-launch batch-1 FFN (k_ffn_fused.hip): the task
 // sizes, the launch order of the six task regions, the task of a workgroup
 // id, and the task table the cache plan writes for it. Shared by the FFN
-// kernel and the plan kernels that write the table.
+// kernel and the plan kernel that writes the table.
 #pragma once
 
 #include "ffn_device.h"
@@ -46,26 +46,36 @@ struct FTask {
   int slice;
 };
 
-// K: 16-byte loads per lane and unit (a unit is d bytes of a neuron's gate and
-// up rows); a wave takes kFL / K units of an h task.
+// The task table of a plan as the plan kernel writes it; grid 0: none.
+// upt: units per h task, kFWaves * kFL / K for K 16-byte loads per lane and
+// unit (a unit is d bytes of a neuron's gate and up rows).
+struct TaskTable {
+  int32_t* tasks;
+  int32_t* task_ids;
+  int d, grid, upt;
+};
+
 // Launch order of the six task regions: (kind, tier) per region.
 constexpr int kOrderKind[6] = {1, 1, 1, 2, 2, 2};
 constexpr int kOrderTier[6] = {1, 2, 3, 1, 2, 3};
 
-template <int K>
-__device__ __forceinline__ FMap make_map_n(int n3, int n2, int n1, int d) {
-  constexpr int U = kFWaves * (kFL / K);  // units per h task
+// Neurons per down task.
+__device__ __forceinline__ int dn_items(int tier) {
+  return (tier == 1 ? kDnRounds1 : tier == 2 ? kDnRounds2 : kDnRounds3) * kFNPR;
+}
+
+__device__ __forceinline__ FMap make_map(int n3, int n2, int n1, int d, int upt) {
   FMap m;
   m.n3 = n3;
   m.n2 = n2;
   m.n1 = n1;
-  m.w1 = (m.n1 + U - 1) / U;
-  m.w2 = (m.n2 + U / 2 - 1) / (U / 2);
-  m.w3 = (m.n3 + U / 4 - 1) / (U / 4);
+  m.w1 = (n1 + upt - 1) / upt;
+  m.w2 = (n2 + upt / 2 - 1) / (upt / 2);
+  m.w3 = (n3 + upt / 4 - 1) / (upt / 4);
   m.n_slices = (d + kFSW - 1) / kFSW;
-  const int u1 = (m.n1 + kDnRounds1 * kFNPR - 1) / (kDnRounds1 * kFNPR);
-  const int u2 = (m.n2 + kDnRounds2 * kFNPR - 1) / (kDnRounds2 * kFNPR);
-  const int u3 = (m.n3 + kDnRounds3 * kFNPR - 1) / (kDnRounds3 * kFNPR);
+  const int u1 = (n1 + dn_items(1) - 1) / dn_items(1);
+  const int u2 = (n2 + dn_items(2) - 1) / dn_items(2);
+  const int u3 = (n3 + dn_items(3) - 1) / dn_items(3);
   int end = 0;
 #pragma unroll
   for (int r = 0; r < 6; ++r) {
@@ -76,18 +86,23 @@ __device__ __forceinline__ FMap make_map_n(int n3, int n2, int n1, int d) {
   }
   return m;
 }
-template <int K>
-__device__ __forceinline__ FMap make_map(const int32_t* counts, int cap, int d) {
-  int n3, n2, n1;
-  work_counts(counts, cap, n3, n2, n1);
-  return make_map_n<K>(n3, n2, n1, d);
+
+// First task of the region of a kind and tier.
+template <int KIND>
+__device__ __forceinline__ int region_start(const FMap& m, int tier) {
+  int start = 0;
+#pragma unroll
+  for (int r = 1; r < 6; ++r)
+    if (kOrderKind[r] == KIND && kOrderTier[r] == tier) start = m.e[r - 1];
+  return start;
 }
 
+// Down tasks: runs of a tier in blocks of 8, slice-major within a block:
+// workgroup b runs on XCD b % 8, so all slices of a run (which read the same
+// scale lines of the run's records) land on one XCD and its L2.
 // Task t in launch order. Work items are tier-major in the plan: FP16, INT8,
 // INT4.
-template <int K>
-__device__ __forceinline__ FTask decode(const FMap& m, int t) {
-  constexpr int U = kFWaves * (kFL / K);
+__device__ __forceinline__ FTask decode(const FMap& m, int t, int upt) {
   FTask k;
   k.kind = 0;
   k.tier = 1;
@@ -113,15 +128,12 @@ __device__ __forceinline__ FTask decode(const FMap& m, int t) {
   const int n = i1 * m.n1 + i2 * m.n2 + i3 * m.n3;
   if (kind == 1) {
     k.kind = 1;
-    const int per = tier == 1 ? U : tier == 2 ? U / 2 : U / 4;
+    const int per = tier == 1 ? upt : tier == 2 ? upt / 2 : upt / 4;
     k.lo = base + per * q;
     k.hi = base + min(per * (q + 1), n);
   } else {
     k.kind = 2;
-    const int per = (tier == 1 ? kDnRounds1 : tier == 2 ? kDnRounds2 : kDnRounds3) * kFNPR;
-    // Runs in blocks of 8, slice-major within a block: workgroup b runs on
-    // XCD b % 8, so all slices of a run (which read the same scale lines of
-    // the run's records) land on one XCD and its L2.
+    const int per = dn_items(tier);
     const int nr = (n + per - 1) / per;
     const int blk = q / (8 * m.n_slices);
     const int within = q - blk * 8 * m.n_slices;
@@ -134,47 +146,60 @@ __device__ __forceinline__ FTask decode(const FMap& m, int t) {
   return k;
 }
 
-
-// The task table, one wave per task: the 32-byte header {kind | tier << 8,
-// first work item, items, slice, then the tier pool's byte offset, first slot
-// id, slot count, record stride} and the slot ids in the order the FFN's
-// waves read them (a down task's items in work order; an h task's units at
-// entry (uw / 4) kFNPR + 4 w + uw % 4 for unit w UW + uw). The table starts
-// with the task count and the zero slot's byte offset. wave / n_waves: this
-// wave among those that write the table; slot(e): the slot of work item e.
-template <int K, typename SlotOf>
-__device__ __forceinline__ void write_task_table(const FMap& m, int grid, const SlotMap& map,
-                                                 int32_t* __restrict__ tasks,
-                                                 int32_t* __restrict__ task_ids, int wave,
-                                                 int n_waves, SlotOf slot) {
-  constexpr int UW = kFL / K;
-  const int n_tasks = m.e[5] < grid ? m.e[5] : grid;
-  if (wave == 0 && (threadIdx.x & 63) == 0) {
-    tasks[0] = n_tasks;
-    tasks[1] = (int32_t)map.zero;
-  }
-  const int lane = threadIdx.x & 63;
-  for (int t = wave; t < n_tasks; t += n_waves) {
-    const FTask k = decode<K>(m, t);
-    const int n = k.hi - k.lo;
-    if (lane == 0) {
-      const int tr = k.tier;
-      int4* h = reinterpret_cast<int4*>(tasks + 4) + 2 * t;
-      h[0] = make_int4(k.kind | (tr << 8), k.lo, n, k.slice);
-      h[1] = make_int4((int)map.base[tr], map.first[tr], map.count[tr], (int)map.stride[tr]);
-    }
-    int32_t* out = task_ids + (int64_t)t * kTaskIds;
-    if (k.kind == 2) {
-      for (int e = lane; e < n; e += 64) out[e] = slot(k.lo + e);
-    } else if (k.kind == 1) {
-      const int upi = k.tier == 3 ? 4 : k.tier == 2 ? 2 : 1;
-      const int item = lane / upi;  // unit lane of the task
-      if (lane < kFWaves * UW && item < n) {
-        const int w = lane / UW, uw = lane % UW;
-        out[(uw >> 2) * kFNPR + 4 * w + (uw & 3)] = slot(k.lo + item);
-      }
-    }
-  }
+// The table: the task count and the zero slot's byte offset; per task t a
+// 32-byte header {kind | tier << 8, first work item, items, slice, then the
+// tier pool's byte offset, first slot id, slot count, record stride}; and the
+// slot ids in the order the FFN's waves read them (a down task's items in
+// work order; an h task's units at entry (uw / 4) kFNPR + 4 w + uw % 4 for
+// unit w UW + uw, UW units per wave).
+__device__ __forceinline__ void write_task_count(const TaskTable& tt, const SlotMap& map, int n) {
+  tt.tasks[0] = n;
+  tt.tasks[1] = (int32_t)map.zero;
 }
+
+__device__ __forceinline__ void write_task_header(const TaskTable& tt, const FMap& m,
+                                                  const SlotMap& map, int t) {
+  const FTask k = decode(m, t, tt.upt);
+  const int tr = k.tier;
+  int4* h = reinterpret_cast<int4*>(tt.tasks + 4) + 2 * t;
+  h[0] = make_int4(k.kind | (tr << 8), k.lo, k.hi - k.lo, k.slice);
+  h[1] = make_int4((int)(tr == 3   ? map.base[3]
+                         : tr == 2 ? map.base[2]
+                                   : map.base[1]),
+                   tr == 3   ? map.first[3]
+                   : tr == 2 ? map.first[2]
+                             : map.first[1],
+                   tr == 3   ? map.count[3]
+                   : tr == 2 ? map.count[2]
+                             : map.count[1],
+                   (int)(tr == 3   ? map.stride[3]
+                         : tr == 2 ? map.stride[2]
+                                   : map.stride[1]));
+}
+
+// Every entry of one work item, the i-th of its tier, in slot `slot`: its
+// units in its h task, and its place in the down task of every slice.
+__device__ __forceinline__ void write_task_items(const TaskTable& tt, const FMap& m, int tier,
+                                                 int i, int slot) {
+  const int upi = tier == 3 ? 4 : tier == 2 ? 2 : 1, uw_n = tt.upt / kFWaves;
+  const int per_h = tt.upt / upi;
+  const int th = region_start<1>(m, tier) + i / per_h;
+  if (th < tt.grid) {
+    int32_t* out = tt.task_ids + (int64_t)th * kTaskIds;
+    for (int v = 0; v < upi; ++v) {
+      const int unit = (i % per_h) * upi + v, w = unit / uw_n, uw = unit % uw_n;
+      out[(uw >> 2) * kFNPR + 4 * w + (uw & 3)] = slot;
+    }
+  }
+  const int n = tier == 3 ? m.n3 : tier == 2 ? m.n2 : m.n1;
+  const int per = dn_items(tier), run = i / per, blk = run >> 3;
+  const int nb = min(8, (n + per - 1) / per - 8 * blk);
+  int t = region_start<2>(m, tier) + blk * 8 * m.n_slices + (run & 7);
+  for (int s = 0; s < m.n_slices && t < tt.grid; ++s, t += nb)
+    tt.task_ids[(int64_t)t * kTaskIds + i % per] = slot;
+}
+
+// The task table of a layer's plan buffer (k_ffn_fused.hip).
+TaskTable plan_task_table(const m2c_layer* L, uint8_t* plan);
 
 }  // namespace m2c

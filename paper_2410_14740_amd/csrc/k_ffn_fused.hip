@@ -678,34 +678,6 @@ hipError_t launch_fused(m2c_layer* L, const uint16_t* x, const int32_t* tasks, f
   return hipGetLastError();
 }
 
-// The task table of a plan (the single cache unit's plan; the per-tier
-// arena's is written with the merge, from the pools' plans).
-template <int K>
-__global__ __launch_bounds__(256) void ffn_tasks_kernel(const int32_t* __restrict__ counts,
-                                                        const int32_t* __restrict__ work_slot,
-                                                        int cap, int d, int grid, SlotMap map,
-                                                        int32_t* __restrict__ tasks,
-                                                        int32_t* __restrict__ task_ids) {
-  const FMap m = make_map<K>(counts, cap, d);
-  write_task_table<K>(m, grid, map, tasks, task_ids,
-                      (int)(blockIdx.x * blockDim.x + threadIdx.x) >> 6,
-                      (int)(gridDim.x * blockDim.x) >> 6, [&](int e) { return work_slot[e]; });
-}
-
-template <int K>
-hipError_t launch_tasks(m2c_layer* L, uint8_t* plan, hipStream_t stream) {
-  const m2c_plan_layout& lay = L->layout;
-  int32_t* tasks = reinterpret_cast<int32_t*>(plan + lay.ffn_tasks);
-  int blocks = (L->ffn_grid + 3) / 4;
-  blocks = blocks < 1 ? 1 : blocks > 256 ? 256 : blocks;
-  hipLaunchKernelGGL(ffn_tasks_kernel<K>, dim3(blocks), dim3(256), 0, stream,
-                     reinterpret_cast<const int32_t*>(plan + lay.counts),
-                     reinterpret_cast<const int32_t*>(plan + lay.work_slot), L->cap,
-                     L->desc.d_model, L->ffn_grid, L->map, tasks,
-                     tasks + task_ids_offset(L->ffn_grid) / 4);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 int ffn_loads_per_unit(int d) {
@@ -748,14 +720,11 @@ int64_t ffn_task_table_bytes(int grid) {
   return task_ids_offset(grid) + (int64_t)grid * kTaskIds * 4;
 }
 
-hipError_t launch_ffn_tasks(m2c_layer* L, uint8_t* plan, hipStream_t stream) {
-  if (!ffn_tasks_used(L) || L->ffn_grid <= 0) return hipSuccess;
-  switch (ffn_loads_per_unit(L->desc.d_model)) {
-    case 1: return launch_tasks<1>(L, plan, stream);
-    case 2: return launch_tasks<2>(L, plan, stream);
-    case 4: return launch_tasks<4>(L, plan, stream);
-    default: return launch_tasks<8>(L, plan, stream);
-  }
+TaskTable plan_task_table(const m2c_layer* L, uint8_t* plan) {
+  if (!ffn_tasks_used(L) || L->ffn_grid <= 0) return TaskTable{nullptr, nullptr, 1, 0, 4};
+  int32_t* tasks = reinterpret_cast<int32_t*>(plan + L->layout.ffn_tasks);
+  return TaskTable{tasks, tasks + task_ids_offset(L->ffn_grid) / 4, (int)L->desc.d_model,
+                   L->ffn_grid, kFWaves * (kFL / ffn_loads_per_unit((int)L->desc.d_model))};
 }
 
 }  // namespace m2c

@@ -191,7 +191,6 @@ void fill_info_layout(m2c_layer* L) {
   P.evicted_ids = take(4 * c);
   P.work_slot = take(4 * (c + m2c::kWorkSlotPad));
   P.work_mask = take(4 * c);
-  L->plan_core_bytes = off;
   P.ffn_tasks = take(m2c::ffn_tasks_used(L)
                          ? m2c::ffn_task_table_bytes(m2c::ffn_fused_grid(
                                (int)L->desc.d_model, (int)c, L->num_cus))
@@ -227,7 +226,6 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
   const m2c_layer_desc& D = L->desc;
   const int64_t d = D.d_model, dff = D.d_ff, r = D.pred_rank, C = D.cache_slots;
   const int64_t cap = L->cap, mb = D.max_batch;
-  const int64_t np = L->pools ? 3 : 1;
   const int n_slices = (int)((d + 511) / 512);
   // (column slices) x (neuron groups) workgroups for the down projection:
   // about 512, at most 64 partial rows, groups of at least 16 neurons.
@@ -240,11 +238,9 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
   struct Piece { void** dst; int64_t bytes; };
   void* p_pred_a; void* p_pred_b; void* p_bias; void* p_z; void* p_scores; void* p_slots;
   void* p_h; void* p_ypart; void* p_slot_of; void* p_slot_key; void* p_slot_tier;
-  void* p_slot_last; void* p_lru; void* p_lru_cur; void* p_new_pos; void* p_work_pos;
-  void* p_vslot; void* p_vold; void* p_fill_pos; void* p_prev_tier; void* p_have; void* p_stats;
-  void* p_status;
-  void* p_gen; void* p_hw; void* p_pool_plan; void* p_abort; void* p_pool_lists;
-  void* p_pool_counts;
+  void* p_slot_last; void* p_lru; void* p_lru_pos; void* p_touch_slot; void* p_touch_pos;
+  void* p_plan_state; void* p_plan_copy; void* p_info; void* p_masks; void* p_chunk_counts;
+  void* p_have; void* p_stats; void* p_status; void* p_gen; void* p_hw;
   Piece pieces[] = {
       // C resident + S staging slots, then one slot that stays zero: padding
       // lanes of the FFN kernels read it instead of branching around loads
@@ -261,23 +257,19 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
       {&p_slot_tier, C},
       {&p_slot_last, C * 4},
       {&p_lru, 2 * C * 4},
-      {&p_lru_cur, 3 * 4},
-      // plan scratch, one set per pool (the pools are planned side by side)
-      {&p_new_pos, np * cap * 4},
-      {&p_work_pos, np * cap * 4},
-      {&p_vslot, np * cap * 4},
-      {&p_vold, np * cap * 4},
-      {&p_fill_pos, np * cap * 4},
-      {&p_prev_tier, np * cap},
+      {&p_lru_pos, 2 * C * 4},
+      {&p_touch_slot, C * 4},
+      {&p_touch_pos, C * 4},
+      {&p_plan_state, m2c::kPlanWords * 4},
+      {&p_plan_copy, m2c::kPlanWords * 4},
+      {&p_info, dff * 4},
+      {&p_masks, mb > 1 ? dff * 4 : 0},
+      {&p_chunk_counts, 16 * ((dff + 1023) / 1024) * 4},
       {&p_have, (C + L->S) * 4},
       {&p_stats, 16 * 8},
       {&p_status, 4},
       {&p_gen, (int64_t)m2c::ffn_fused_grid((int)d, (int)cap, L->num_cus) * 8},
       {&p_hw, cap * 8},
-      {&p_pool_plan, L->pools ? 3 * L->plan_core_bytes : 0},
-      {&p_abort, 4},
-      {&p_pool_lists, L->pools ? 3 * dff * 4 : 0},
-      {&p_pool_counts, L->pools ? 3 * 32 * 4 : 0},
   };
   int64_t total = 0;
   int64_t offs[sizeof(pieces) / sizeof(pieces[0])];
@@ -304,25 +296,21 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
   L->st.slot_tier = (uint8_t*)p_slot_tier;
   L->st.slot_last = (int32_t*)p_slot_last;
   L->st.lru = (int32_t*)p_lru;
-  L->st.lru_cur = (int32_t*)p_lru_cur;
-  L->st.new_pos = (int32_t*)p_new_pos;
-  L->st.work_pos = (int32_t*)p_work_pos;
-  L->st.vict_slot = (int32_t*)p_vslot;
-  L->st.vict_old = (int32_t*)p_vold;
-  L->st.fill_pos = (int32_t*)p_fill_pos;
-  L->st.prev_tier = (uint8_t*)p_prev_tier;
+  L->st.lru_pos = (int32_t*)p_lru_pos;
+  L->st.touch_slot = (int32_t*)p_touch_slot;
+  L->st.touch_pos = (int32_t*)p_touch_pos;
+  L->st.plan_state = (int32_t*)p_plan_state;
+  L->st.plan_copy = (int32_t*)p_plan_copy;
+  L->st.info = (uint32_t*)p_info;
+  L->st.masks = (uint32_t*)p_masks;
+  L->st.chunk_counts = (int32_t*)p_chunk_counts;
   L->st.slot_rec = (int32_t*)p_have;
   L->st.stats = (unsigned long long*)p_stats;
   L->st.status = (int32_t*)p_status;
   L->st.ffn_gen = (unsigned long long*)p_gen;
   L->st.ffn_hw = (unsigned long long*)p_hw;
-  L->pool_plan = (uint8_t*)p_pool_plan;
-  L->plan_abort = (int32_t*)p_abort;
-  L->pool_lists = (int32_t*)p_pool_lists;
-  L->pool_counts = (int32_t*)p_pool_counts;
   L->info.device_bytes = total;
   HIPOK(hipMemset(L->slots + L->map.zero, 0, L->info.slot_bytes), "clear the zero slot");
-  HIPOK(hipMemset(L->plan_abort, 0, 4), "clear the plan abort word");
   HIPOK(hipMemset(L->st.status, 0, 4), "clear the status word");
   L->ffn_grid = m2c::ffn_fused_grid((int)d, (int)cap, L->num_cus);
   HIPOK(hipMemset(L->st.ffn_gen, 0, (size_t)(L->ffn_grid > 0 ? L->ffn_grid : 1) * 8),

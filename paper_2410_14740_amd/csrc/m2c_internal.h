@@ -33,20 +33,29 @@ struct Store {
   int64_t bytes = 0;
 };
 
-// Offsets of the per-layer device scratch used by the plan kernel.
+// Words of the plan's device state: a serial number per plan (the stamp of the
+// slots it touches; kept on the device, so a replayed graph advances it), which
+// of the two LRU orders is current, and the slots of each pool that were ever
+// filled.
+enum { kPlanSerial, kPlanCur, kPlanFilled, kPlanWords = kPlanFilled + 3 };
+
+// Per-layer device state of the plan, the fill and the FFN. With tier pools
+// the tables of the pools lie back to back (FP16, INT8, INT4) over the C
+// resident slots; LRU orders and places hold such concatenated slot ids.
 struct DeviceState {
-  int32_t* slot_of = nullptr;    // [d_ff]
+  int32_t* slot_of = nullptr;    // [d_ff] slot in its pool or -1 (tier pools: one table per pool)
   int32_t* slot_key = nullptr;   // [C]
   uint8_t* slot_tier = nullptr;  // [C]
   int32_t* slot_last = nullptr;  // [C]
-  int32_t* lru = nullptr;        // [2][C] ping-pong LRU order
-  int32_t* lru_cur = nullptr;    // [1]
-  int32_t* new_pos = nullptr;    // [cap] plan scratch: req position of the j-th NEW
-  int32_t* work_pos = nullptr;   // [cap] plan scratch: work position of req p
-  int32_t* vict_slot = nullptr;  // [cap] plan scratch
-  int32_t* vict_old = nullptr;   // [cap] plan scratch
-  int32_t* fill_pos = nullptr;   // [cap] plan scratch: fill position of req p (-1 for hits)
-  uint8_t* prev_tier = nullptr;  // [cap] plan scratch: tier a REFILL's slot held before the step
+  int32_t* lru = nullptr;        // [2][C] slots by (last use, slot), current and next
+  int32_t* lru_pos = nullptr;    // [2][C] place of each slot in that order
+  int32_t* touch_slot = nullptr; // [C] serial of the last plan that touched the slot
+  int32_t* touch_pos = nullptr;  // [C] the same by place in the order that plan read
+  int32_t* plan_state = nullptr; // [kPlanWords]
+  int32_t* plan_copy = nullptr;  // [kPlanWords] plan_state as the running plan found it
+  uint32_t* info = nullptr;      // [d_ff] plan scratch: the neuron's word
+  uint32_t* masks = nullptr;     // [d_ff] plan scratch: row masks (max_batch > 1)
+  int32_t* chunk_counts = nullptr;  // plan scratch: counts per field and chunk of neurons
   int32_t* slot_rec = nullptr;   // [C + S] record a slot's bytes hold, 4 * neuron + tier (-1: none), kept by the fill
   unsigned long long* stats = nullptr;  // [16] cumulative counters
   int32_t* status = nullptr;           // [1] M2C_STATUS_* bits set by kernels
@@ -102,14 +111,6 @@ struct m2c_layer {
   int pool_rf[4] = {0, 0, 0, 0};  // first resident table index of the pool
   m2c::SlotMap map;               // slot id -> byte offset, by tier
   int64_t arena_bytes = 0;        // pools + zero slot
-  uint8_t* pool_plan = nullptr;   // [3][plan_core_bytes] the pools' own plans
-  // per-tier arena: each pool's required neurons of a step, per chunk of
-  // 1024 neurons in ascending id ([3][d_ff], FP16 first; chunk j from j * 1024),
-  // and their counts ([3][32])
-  int32_t* pool_lists = nullptr;
-  int32_t* pool_counts = nullptr;
-  int64_t plan_core_bytes = 0;    // a plan without the one-launch FFN's task table
-  int32_t* plan_abort = nullptr;  // [1] set when a step's required set overflowed
 };
 
 namespace m2c {
@@ -152,7 +153,7 @@ hipError_t launch_reset(m2c_layer* L, hipStream_t stream);
 hipError_t launch_fill(const m2c_layer* L, const uint8_t* plan, const uint8_t* const host[4],
                        hipStream_t stream);
 hipError_t launch_poison_fill_slots(const m2c_layer* L, const uint8_t* plan, hipStream_t stream);
-// The state and plan pointers of tier t's pool (M2C_FLAG_TIER_POOLS).
+// The state with the slot tables of tier t's pool (M2C_FLAG_TIER_POOLS).
 DeviceState pool_state(const m2c_layer* L, int t);
 hipError_t launch_ffn(m2c_layer* L, const uint16_t* x, int batch, const uint8_t* plan, float* y,
                       hipStream_t stream);
@@ -163,12 +164,10 @@ hipError_t launch_ffn_split(m2c_layer* L, const uint16_t* x, const uint8_t* plan
 bool ffn_fused_supported(const m2c_layer* L);
 int ffn_fused_grid(int d_model, int cap, int num_cus);  // workgroups (and gen counters) of the one-launch FFN
 // The one-launch FFN's task table in a plan: whether the layer's plans carry
-// one (batch-1 FFN calls use that kernel), its bytes for a grid, and the
-// kernel that writes it from the plan's counts and work order.
+// one (batch-1 FFN calls use that kernel) and its bytes for a grid.
 bool ffn_tasks_used(const m2c_layer* L);
 int ffn_loads_per_unit(int d);  // K of the one-launch FFN: 16-byte loads per lane and unit
 int64_t ffn_task_table_bytes(int grid);
-hipError_t launch_ffn_tasks(m2c_layer* L, uint8_t* plan, hipStream_t stream);
 hipError_t launch_ffn_fused(m2c_layer* L, const uint16_t* x, const uint8_t* plan, float* y,
                             hipStream_t stream);
 
