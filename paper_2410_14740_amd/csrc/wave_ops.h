@@ -37,6 +37,58 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
+// v of lane l ^ OFF of the row of 16 (OFF 1, 2, 4, 8).
+template <int OFF>
+__device__ __forceinline__ float row_xor(float v) {
+  const int u = __float_as_int(v);
+  if constexpr (OFF == 8) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, u, kDppRowRor + 8, 0xf, 0xf, false));
+  } else if constexpr (OFF == 4) {  // l ^ 7 (mirror of 8 lanes), then ^ 3 (quad reversed)
+    const int m = __builtin_amdgcn_update_dpp(0, u, 0x141, 0xf, 0xf, false);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, m, 0x1b, 0xf, 0xf, false));
+  } else if constexpr (OFF == 2) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, u, 0x4e, 0xf, 0xf, false));
+  } else {
+    static_assert(OFF == 1, "lane distances of a row of 16");
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, u, 0xb1, 0xf, 0xf, false));
+  }
+}
+
+// One level of a cross-lane sum for two values at once: lanes without bit OFF
+// get u[l] + u[l ^ OFF], lanes with it v[l] + v[l ^ OFF].
+template <int OFF>
+__device__ __forceinline__ float xor_fold(float u, float v) {
+  if constexpr (OFF == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  } else if constexpr (OFF == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(u), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  } else {
+    const float a = u + row_xor<OFF>(u), b = v + row_xor<OFF>(v);
+    return (threadIdx.x & OFF) ? b : a;
+  }
+}
+
+// The xor-tree sums (p[l] + p[l ^ off] for off = OFF, OFF / 2, .. 1) of N
+// values, N a power of two, every level on half the registers of the one
+// before while there are two: afterwards v[i] holds value (i << F) + j in the
+// lanes whose bits OFF, OFF / 2, .. (F of them) are the bits 0, 1, .. of j,
+// F = min(log2 N, levels).
+template <int OFF, int N>
+__device__ __forceinline__ void xor_tree(float* v) {
+  if constexpr (OFF >= 1) {
+    if constexpr (N > 1) {
+#pragma unroll
+      for (int i = 0; i < N / 2; ++i) v[i] = xor_fold<OFF>(v[2 * i], v[2 * i + 1]);
+      xor_tree<OFF / 2, N / 2>(v);
+    } else {
+      v[0] = xor_fold<OFF>(v[0], v[0]);
+      xor_tree<OFF / 2, 1>(v);
+    }
+  }
+}
+
 // Largest value of each row of 16 lanes, in every lane of the row.
 __device__ __forceinline__ uint32_t row_max(uint32_t v) {
   v = max(v, dpp0<kDppRowRor + 8>(v));
