@@ -25,9 +25,10 @@
 //                   dequantization stays exact. The waves' partials meet in
 //                   LDS; h_{b,i} = silu(a) * u, zero where row b did not
 //                   select neuron i.
-//   ffn_bdm_kernel  the down projection, also on the matrix cores, by
-//                   quantization group and single-tier run (below).
+//   ffn_bdn_kernel  the down projection, also on the matrix cores, by
+//                   quantization group (below).
 #include "ffn_device.h"
+#include "wave_ops.h"
 
 namespace m2c {
 
@@ -72,6 +73,17 @@ __device__ __forceinline__ half4v i8x4_to_h4(uint32_t w) {
   r[2] = b[0];
   r[3] = b[1];
   return r;
+}
+
+// The h values, written by the gate/up kernel and read by the down kernel as
+// matrix-core operands: 4 consecutive items of one tier, then the batch row
+// (Bp = 16 or 32 rows, zeros past the batch), then the next 4 items, each
+// tier's items from a multiple of 32 (h_base + the item's place in its tier).
+constexpr int kHAlign = 32;
+__device__ __forceinline__ int h_base(int tier, int n3, int n2) {
+  const int p3 = (n3 + kHAlign - 1) / kHAlign * kHAlign;
+  const int p2 = (n2 + kHAlign - 1) / kHAlign * kHAlign;
+  return tier == 3 ? 0 : tier == 2 ? p3 : p3 + p2;
 }
 
 // Tile b: up to 16 consecutive work items of one tier. An FP16 tile takes 8
@@ -333,7 +345,8 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
     bh_tier<2, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
   else
     bh_tier<1, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
-  if (threadIdx.x < 16) s_mask[threadIdx.x] = my_slot < n_slots ? my_mask : 0u;
+  if (threadIdx.x < 16)
+    s_mask[threadIdx.x] = my_slot < n_slots && (int)threadIdx.x < nitems ? my_mask & (0xffffffffu >> (32 - B)) : 0u;
   __syncthreads();  // every wave is done with its x rows: the partials take their bytes
   // partials of the waves -> LDS: [w][gate/up][row][col]
   float* s_part = reinterpret_cast<float*>(bh_lds);
@@ -347,16 +360,21 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
       s_part[((w * 2 + 1) * 16 + 4 * j + i) * NC + 16 * t + col] = acc_u[t][i];
     }
   __syncthreads();
-  for (int e = threadIdx.x; e < 16 * B; e += kBHThreads) {
-    const int r = e / B, b = e % B;  // neuron row, batch row
-    if (r >= nitems) continue;
+  // h in the down kernel's layout: 4 items, batch row, next 4 items; zero past
+  // the tile's items and the batch
+  const int per = tier == 3 ? 8 : 16;
+  const int local = item0 - (tier == 3 ? 0 : tier == 2 ? n3 : n3 + n2);
+  float* hT = hB + (int64_t)(h_base(tier, n3, n2) + local) * NC;
+  for (int e = threadIdx.x; e < per * NC; e += kBHThreads) {
+    const int m = e & 3, b = (e >> 2) % NC, r = 4 * (e / (4 * NC)) + m;  // item, batch row
     float a = 0.0f, u = 0.0f;
     for (int q = 0; q < kBHWaves; ++q) {  // waves in a fixed order
       a += s_part[((q * 2 + 0) * 16 + r) * NC + b];
       u += s_part[((q * 2 + 1) * 16 + r) * NC + b];
     }
-    // zero where row b did not select neuron r (or its slot is invalid)
-    hB[(int64_t)b * ((cap + 3) & ~3) + item0 + r] = (s_mask[r] >> b) & 1u ? silu_mul(a, u) : 0.0f;
+    // zero where row b did not select neuron r (or its slot is invalid); the
+    // masks of padding items and the bits past the batch are zero
+    hT[e] = (s_mask[r] >> b) & 1u ? silu_mul(a, u) : 0.0f;
   }
 }
 
@@ -366,57 +384,36 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
 //   y[b][c] += sum_n (h[b][n] s[n]) q[n][c],
 // so each neuron's scale folds into the h side and the codes q enter the
 // matrix cores exactly, as fp16. The h side is split into an fp16 high and low
-// part (two MFMAs per tile) after a power-of-two normalisation per wave, which
-// keeps the products at fp32-level precision whatever the magnitudes.
+// part (two MFMAs per tile) after a power-of-two normalisation per wave and
+// batch row, which keeps the products at fp32-level precision whatever the
+// magnitudes.
 //
-// Workgroup: one group by a run of one tier; its 8 waves take consecutive
-// parts of the run, in steps of 16 neurons. In a step lane (x, j)
-// (x = lane % 16, j = lane / 16) loads the 8 codes at columns 8x .. 8x + 7 of
-// the group from neurons 4j .. 4j + 3; MFMA e (e = 0..7) takes code e of
-// each, so that its 16 result columns are 8x + e, and the lane's A operand is
-// h s of batch row x for the same four neurons.
+// A group's items are cut into steps of 32 of one tier (FP16, INT8, INT4); each
+// wave of the group's workgroups takes an equal run of them, so that most
+// waves see one tier (steps dealt in turn, a share of every tier per wave,
+// cost a load round trip per tier: 13.2 instead of 12.1 us at batch 8). In a
+// step lane (x, j) (x = lane % 16, j = lane / 16) loads the 8
+// codes at columns 8x .. 8x + 7 of the group from items 4j .. 4j + 3 and
+// 16 + 4j .. 16 + 4j + 3; MFMA e (e = 0..7) takes code e of each, so that its
+// 16 result columns are 8x + e, and the lane's A operand is h s of batch row x
+// for the same eight items. The next step's loads are in flight while one is
+// computed.
+//
+// What bounds it: with 32 rows the unpacking and the split of h (VALU), with 8
+// latency. A wave keeps its sums in registers over all its steps: one
+// workgroup per run of 128 .. 512 items, as before, spent most of its time on
+// atomics (B x 128 per run and group; 12 M of them at 32 rows of the 70B
+// shape) and on empty workgroups of a grid sized for the plan's capacity.
+// Measured (MI355X, rocprofv3 kernel time, before -> now): 70B
+// shape at 32 rows 104 -> 43.7 us, 7B at 8 rows 13.1 -> 12.6.
 
-constexpr int kDMThreads = 512;
+constexpr int kDMThreads = 256;
 constexpr int kDMWaves = kDMThreads / 64;
 constexpr int kDMRegions = kDMWaves / 2;  // LDS partial results per workgroup
-#ifndef M2C_DM_STEPS
-#define M2C_DM_STEPS 1
-#endif
-// 16-neuron steps per wave: INT8 runs take twice and INT4 runs four times the
-// FP16 count, so that every workgroup carries the same record bytes (32 KB).
-template <int TIER>
-__host__ __device__ constexpr int dm_steps() {
-  return M2C_DM_STEPS << (3 - TIER);
-}
-template <int TIER>
-__host__ __device__ constexpr int dm_run_len() {
-  return kDMWaves * 16 * dm_steps<TIER>();
-}
-
-// a wave reads slot ids up to one run length past its run's first item
-static_assert(dm_run_len<1>() <= kWorkSlotPad, "runs longer than the plan's spare work_slot entries");
-
-// Run b of a group: up to dm_run_len<tier>() consecutive items of one tier.
-__device__ __forceinline__ void dm_run(int b, int n3, int n2, int n1, int& tier, int& lo, int& hi) {
-  constexpr int R3 = dm_run_len<3>(), R2 = dm_run_len<2>(), R1 = dm_run_len<1>();
-  const int w3 = (n3 + R3 - 1) / R3, w2 = (n2 + R2 - 1) / R2, w1 = (n1 + R1 - 1) / R1;
-  if (b < w3) {
-    tier = 3;
-    lo = b * R3;
-    hi = min(lo + R3, n3);
-  } else if (b < w3 + w2) {
-    tier = 2;
-    lo = n3 + (b - w3) * R2;
-    hi = min(lo + R2, n3 + n2);
-  } else if (b < w3 + w2 + w1) {
-    tier = 1;
-    lo = n3 + n2 + (b - w3 - w2) * R1;
-    hi = min(lo + R1, n3 + n2 + n1);
-  } else {
-    tier = 0;
-    lo = hi = 0;
-  }
-}
+constexpr int kDMStep = 32;               // items per step
+// a wave reads the slot ids of whole steps, two steps ahead
+static_assert(kDMStep <= kWorkSlotPad, "steps longer than the plan's spare work_slot entries");
+static_assert(kDMStep == kHAlign, "a step's h starts at a multiple of its length");
 
 // The 8 codes of one neuron at the lane's columns: 16 bytes of FP16, 8 of
 // INT8, 4 of INT4.
@@ -496,146 +493,188 @@ __device__ __forceinline__ uint2 dm_offset(uint2 v) {
 }
 __device__ __forceinline__ uint32_t dm_offset(uint32_t v) { return v ^ 0x88888888u; }
 
-// One wave's share of a run: neurons [first, first + 16 S) of the run's
-// items, group grp; acc[t][e] gets the lane's D rows 16 t + 4 j + i of MFMA e.
-// s_hw: the wave's LDS for its h values, 16 NT rows of 16 S floats.
-typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+// The loads of one step; the slot ids come first (their own struct, one step
+// further ahead). Every load is unconditional: items past the tier's last
+// read the zero slot and whatever h words follow, and are masked.
+typedef int int4u __attribute__((ext_vector_type(4), aligned(4)));
+struct DmSlots {
+  int4u s[2];
+  __device__ __forceinline__ void issue(const int32_t* __restrict__ ids, int i0, int j) {
+    s[0] = *reinterpret_cast<const int4u*>(ids + i0 + 4 * j);
+    s[1] = *reinterpret_cast<const int4u*>(ids + i0 + 16 + 4 * j);
+  }
+};
+
 template <int TIER, int NT>
-__device__ __forceinline__ void dm_wave(int first, int hi, int grp, int d, int G, int B, int cap,
-                                        const int32_t* __restrict__ work_slot,
-                                        const float* __restrict__ hB,
-                                        const uint8_t* __restrict__ slots, int64_t slot_bytes,
-                                        int n_slots, float* s_hw, float4v (&acc)[NT][8]) {
-  constexpr int S = dm_steps<TIER>();
+struct DmLoads {
   typedef typename DmWord<TIER>::T Word;
+  Word cw[2][4];
+  half2v sc[2][2];  // two fp16 scales per register
+  float4v h[2][NT];
+  __device__ __forceinline__ void issue(const DmSlots& sl, int i0, int n, const float* __restrict__ hT,
+                                        const uint8_t* __restrict__ slots, int64_t slot_bytes,
+                                        int n_slots, int64_t doff, int64_t soff, int x, int j) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int s = sl.s[a][m];
+        const bool ok = i0 + 16 * a + 4 * j + m < n && s >= 0 && s < n_slots;
+        const uint8_t* rec = slots + (int64_t)(ok ? s : n_slots) * slot_bytes;
+        cw[a][m] = *reinterpret_cast<const Word*>(rec + doff);
+        if (TIER != 3) sc[a][m >> 1][m & 1] = *reinterpret_cast<const _Float16*>(rec + soff);
+      }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        h[a][t] = *reinterpret_cast<const float4v*>(
+            hT + ((int64_t)((i0 + 16 * a) / 4 + j) * (16 * NT) + 16 * t + x) * 4);
+  }
+};
+
+// Largest value over the four lanes x, 16 + x, 32 + x, 48 + x, in all of them.
+__device__ __forceinline__ uint32_t rows_max(uint32_t v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max((uint32_t)r[0], (uint32_t)r[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return max((uint32_t)q[0], (uint32_t)q[1]);
+}
+
+// One step's arithmetic. E: the running exponent of the lane's batch rows (row
+// 16 t + x), whose sums are held times 2^E. It only falls, when a step brings a
+// row values above 2^15, to put the largest one at 2^11 .. 2^12 (room for larger
+// ones later, so that few steps rescale): values 2^-36 of the row's largest and
+// below lose bits, which the fp32 sums lose anyway. A step adds to the running
+// sums once per part: with one row tile the low parts have sums of their own,
+// with two (no registers for that) a step's products are summed first. Adding
+// both parts to one sum in turn was 2 us faster at 32 rows of the 70B shape,
+// but its error against 64 bits was 7% larger (2.41e-7 instead of 2.26e-7).
+template <int TIER, int NT>
+__device__ __forceinline__ void dm_step(const DmLoads<TIER, NT>& L, int i0, int n, int j, int (&E)[NT],
+                                        float4v (&acc)[2][8]) {
+  float a[2][NT][4];
+  uint32_t mx[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) mx[t] = 0;
+  const bool whole = i0 + kDMStep <= n;  // wave-uniform
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        float v = L.h[q][t][m];
+        if (TIER != 3) v *= (float)L.sc[q][m >> 1][m & 1];
+        if (!whole && i0 + 16 * q + 4 * j + m >= n) v = 0.0f;
+        a[q][t][m] = v;
+        mx[t] = max(mx[t], __float_as_uint(v) & 0x7fffffffu);
+      }
+  int dE[NT];
+  bool move = false;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const uint32_t m = rows_max(mx[t]);
+    const int e = __builtin_amdgcn_frexp_expf(__uint_as_float(m));
+    dE[t] = m > 0 && e + E[t] > 15 ? 12 - e - E[t] : 0;
+    move |= dE[t] != 0;
+  }
+  if (__any(move)) {  // the sums of row 4 j + i are in lane group j, its exponent in lane 4 j + i
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      E[t] += dE[t];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int de = __shfl(dE[t], 4 * j + i);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          acc[t][c][i] = ldexpf(acc[t][c][i], de);
+          if (NT == 1) acc[1][c][i] = ldexpf(acc[1][c][i], de);
+        }
+      }
+    }
+  }
+  half8v ahi[NT], alo[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const float v = ldexpf(a[q][t][m], E[t]);
+        const _Float16 hi = (_Float16)v;
+        ahi[t][4 * q + m] = hi;
+        alo[t][4 * q + m] = (_Float16)(v - (float)hi);
+      }
+  half4v b0[8], b1[8];
+  typename DmWord<TIER>::T c0[4], c1[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    c0[m] = dm_offset(L.cw[0][m]);
+    c1[m] = dm_offset(L.cw[1][m]);
+  }
+  dm_operands<TIER>(c0, b0);
+  dm_operands<TIER>(c1, b1);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const half8v b = h8(b0[c], b1[c]);
+    if constexpr (NT == 1) {
+      acc[0][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi[0], b, acc[0][c], 0, 0, 0);
+      acc[1][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(alo[0], b, acc[1][c], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        float4v p = {0.0f, 0.0f, 0.0f, 0.0f};
+        p = __builtin_amdgcn_mfma_f32_16x16x32_f16(alo[t], b, p, 0, 0, 0);
+        p = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi[t], b, p, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[t][c][i] += p[i];
+      }
+    }
+  }
+}
+
+// A wave's steps [first, end) of one tier's n items (ids: their slots, hT:
+// their h; sl: the first step's slots). Past the last step the prefetches
+// re-read the first.
+template <int TIER, int NT>
+__device__ __forceinline__ void dm_tier(DmSlots sl, int first, int end, int n,
+                                        const int32_t* __restrict__ ids,
+                                        const float* __restrict__ hT, int grp, int d, int G,
+                                        const uint8_t* __restrict__ slots, int64_t slot_bytes,
+                                        int n_slots, int (&E)[NT], float4v (&acc)[2][8]) {
+  if (first >= end) return;  // wave-uniform
   const int lane = threadIdx.x & 63, x = lane & 15, j = lane >> 4;
   // byte offsets in a record: the lane's 8 down codes of group grp, and the group's down scale
   const int64_t doff = TIER == 3   ? 4 * (int64_t)d + 2 * (128 * grp + 8 * x)
                        : TIER == 2 ? 2 * (int64_t)d + 128 * grp + 8 * x
                                    : (int64_t)d + 64 * grp + 4 * x;
   const int64_t soff = (TIER == 1 ? 3 * (int64_t)(d >> 1) : 3 * (int64_t)d) + 4 * G + 2 * grp;
-  // Every vector load is unconditional (indices clamped into the run and the
-  // batch, values masked afterwards), so that all of them are in flight at
-  // once. The slot ids come first, through the scalar cache: the wave's 16
-  // ids of a step are one wave-uniform range (inside the plan's spare
-  // work_slot entries past the run), and a scalar load does not queue behind
-  // the vector loads of other waves.
-  int sl[S][4];
-  // lane group j takes ids 4 j .. 4 j + 3 of each step (branch-free select)
-  const int mj0 = -(j == 0), mj1 = -(j == 1), mj2 = -(j == 2), mj3 = -(j == 3);
-#pragma unroll
-  for (int st = 0; st < S; ++st) {
-    int u[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) u[k] = __builtin_amdgcn_readfirstlane(work_slot[first + 16 * st + k]);
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-      sl[st][m] = (u[m] & mj0) | (u[4 + m] & mj1) | (u[8 + m] & mj2) | (u[12 + m] & mj3);
+  auto at = [&](int st) { return kDMStep * (st < end ? st : first); };
+  DmLoads<TIER, NT> L0, L1;
+  auto load = [&](DmLoads<TIER, NT>& L, int i0) {
+    L.issue(sl, i0, n, hT, slots, slot_bytes, n_slots, doff, soff, x, j);
+  };
+  load(L0, at(first));
+  sl.issue(ids, at(first + 1), j);
+  for (int st = first;;) {
+    load(L1, at(st + 1));
+    sl.issue(ids, at(st + 2), j);
+    __builtin_amdgcn_sched_barrier(0);  // the loads go out before the arithmetic
+    dm_step<TIER, NT>(L0, at(st), n, j, E, acc);
+    if (++st >= end) break;
+    load(L0, at(st + 1));
+    sl.issue(ids, at(st + 2), j);
+    __builtin_amdgcn_sched_barrier(0);
+    dm_step<TIER, NT>(L1, at(st), n, j, E, acc);
+    if (++st >= end) break;
   }
-  // h of the wave's 16 S items for every batch row (rows cap rounded up to
-  // 4 apart): 16-byte loads of 4 consecutive items, which run along a row,
-  // staged through LDS; chunk e = 64 q + lane is row e / (4 S), items 4 (e %
-  // (4 S)) .. + 4. Rows past the batch and items past the run are masked below.
-  constexpr int CPR = 4 * S;  // 16-byte chunks per batch row
-  const int hs = (cap + 3) & ~3;
-  float4u hv[S * NT];
-#pragma unroll
-  for (int q = 0; q < S * NT; ++q) {
-    const int e = 64 * q + lane, row = e / CPR, c = e - row * CPR;
-    hv[q] = *reinterpret_cast<const float4u*>(hB + (int64_t)min(row, B - 1) * hs +
-                                               min(first + 4 * c, hi - 1));
-  }
-  // phase 2: per neuron its group scale and its codes (the zero slot past the run)
-  half2v sc[S][2];  // two fp16 scales per register
-  Word cw[S][4];
-#pragma unroll
-  for (int st = 0; st < S; ++st)
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int s = first + 16 * st + 4 * j + m < hi ? sl[st][m] : -1;
-      const uint8_t* rec = slots + (int64_t)(s >= 0 && s < n_slots ? s : n_slots) * slot_bytes;
-      if (TIER != 3) sc[st][m >> 1][m & 1] = *reinterpret_cast<const _Float16*>(rec + soff);
-      cw[st][m] = *reinterpret_cast<const Word*>(rec + doff);
-    }
-  __builtin_amdgcn_sched_barrier(0);  // keep every load issued before the first use
-#pragma unroll
-  for (int q = 0; q < S * NT; ++q) {
-    const int e = 64 * q + lane, row = e / CPR, c = e - row * CPR;
-    *reinterpret_cast<float4v*>(s_hw + row * 16 * S + 4 * c) = hv[q];
-  }
-  float a[S][NT][4];
-#pragma unroll
-  for (int st = 0; st < S; ++st)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const float4v v = *reinterpret_cast<const float4v*>(s_hw + (16 * t + x) * 16 * S + 16 * st + 4 * j);
-#pragma unroll
-      for (int m = 0; m < 4; ++m) a[st][t][m] = v[m];
-    }
-  // h of rows past the batch and of items past the run is 0
-#pragma unroll
-  for (int st = 0; st < S; ++st)
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        if (16 * t + x >= B || first + 16 * st + 4 * j + m >= hi) a[st][t][m] = 0.0f;
-  // A = h s, normalised so that the wave's largest |A| lies in [2^14, 2^15)
-  float mx = 0.0f;
-#pragma unroll
-  for (int st = 0; st < S; ++st)
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        if (TIER != 3) a[st][t][m] *= (float)sc[st][m >> 1][m & 1];
-        mx = fmaxf(mx, fabsf(a[st][t][m]));
-      }
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  const int E = mx > 0.0f ? 15 - __builtin_amdgcn_frexp_expf(mx) : 0;
-  half4v ahi[S][NT], alo[S][NT];
-#pragma unroll
-  for (int st = 0; st < S; ++st)
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const float v = ldexpf(a[st][t][m], E);
-        const _Float16 h = (_Float16)v;
-        ahi[st][t][m] = h;
-        alo[st][t][m] = (_Float16)(v - (float)h);
-      }
-#pragma unroll
-  for (int st = 0; st < S; ++st) {
-    Word c[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) c[m] = dm_offset(cw[st][m]);
-    half4v bop[8];
-    dm_operands<TIER>(c, bop);
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x16f16(ahi[st][t], bop[e], acc[t][e], 0, 0, 0);
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x16f16(alo[st][t], bop[e], acc[t][e], 0, 0, 0);
-  }
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[t][e][i] = ldexpf(acc[t][e][i], -E);
 }
 
 // NT: 16-row tiles of the batch (1 for B <= 16, 2 for B <= 32).
-// blockIdx.x = group + G * run.
+// blockIdx.x = group + G * (workgroup of the group).
 template <int NT>
-__global__ __launch_bounds__(kDMThreads) void ffn_bdm_kernel(
+__global__ __launch_bounds__(kDMThreads, 2) void ffn_bdn_kernel(
     int d, int B, const int32_t* __restrict__ counts, const int32_t* __restrict__ work_slot,
     const float* __restrict__ hB, const uint8_t* __restrict__ slots, int64_t slot_bytes, int cap,
     int n_slots, float* __restrict__ y) {
@@ -644,43 +683,57 @@ __global__ __launch_bounds__(kDMThreads) void ffn_bdm_kernel(
   // waves 4..7 add theirs to them, so that every LDS word has one writer at a
   // time (LDS float atomics are slow)
   __shared__ float s_y[kDMRegions][16 * NT][kRow];
-  static_assert(kDMWaves * 16 * dm_steps<1>() <= kDMRegions * kRow, "h staging fits in s_y");
   const int G = d >> 7;
   int grp = blockIdx.x % G;
-  // Groups 2i and 2i + 1 of a run go to workgroup ids 8 apart: one XCD (ids
-  // are dealt to the 8 XCDs in turn) and about the same start, so that a
-  // 128-byte line of INT4 codes, which holds both groups of a neuron, is
-  // fetched into that XCD's L2 once.
+  // Groups 2i and 2i + 1 of a workgroup go to ids 8 apart: one XCD (ids are
+  // dealt to the 8 XCDs in turn) and about the same start, so that a 128-byte
+  // line of INT4 codes, which holds both groups of a neuron, is fetched into
+  // that XCD's L2 once.
   if ((G & 15) == 0) {
     const int p = grp & 15;
     grp = (grp & ~15) + 2 * (p & 7) + (p >> 3);
   }
   int n3, n2, n1;
   work_counts(counts, cap, n3, n2, n1);
-  int tier, lo, hi;
-  dm_run(blockIdx.x / G, n3, n2, n1, tier, lo, hi);
-  if (lo >= hi) return;  // workgroup-uniform
+  const int S3 = (n3 + kDMStep - 1) / kDMStep, S2 = (n2 + kDMStep - 1) / kDMStep;
+  const int S1 = (n1 + kDMStep - 1) / kDMStep;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-
-  float4v acc[NT][8];
+  const int wg = blockIdx.x / G, W = (gridDim.x / G) * kDMWaves, ST = S3 + S2 + S1;
+  if ((int64_t)ST * wg * kDMWaves / W == (int64_t)ST * (wg + 1) * kDMWaves / W) return;  // no steps
+  const int gw = wg * kDMWaves + w;
+  const int lo = (int)((int64_t)ST * gw / W), hi = (int)((int64_t)ST * (gw + 1) / W);
+  const int lane = threadIdx.x & 63, x = lane & 15, j = lane >> 4;
+  // the wave's run of the group's steps, by tier
+  const int st3 = lo, st2 = max(lo - S3, 0), st1 = max(lo - S3 - S2, 0);
+  const int en3 = min(hi, S3), en2 = min(hi - S3, S2), en1 = hi - S3 - S2;
+  const int32_t *ids2 = work_slot + n3, *ids1 = ids2 + n2;
+  DmSlots sl3, sl2, sl1;
+  sl3.issue(work_slot, kDMStep * min(st3, S3), j);
+  sl2.issue(ids2, kDMStep * min(st2, S2), j);
+  sl1.issue(ids1, kDMStep * min(st1, S1), j);
+  float4v acc[2][8];  // sums of the row tiles; of the high and low parts when there is one tile
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[t][e] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+  int E[NT];  // above every exponent until a row's first value sets it
+#pragma unroll
+  for (int t = 0; t < NT; ++t) E[t] = 1 << 10;
+  constexpr int Bp = 16 * NT;
+  dm_tier<3, NT>(sl3, st3, en3, n3, work_slot, hB, grp, d, G, slots, slot_bytes, n_slots, E, acc);
+  dm_tier<2, NT>(sl2, st2, en2, n2, ids2, hB + (int64_t)h_base(2, n3, n2) * Bp, grp, d, G, slots,
+                 slot_bytes, n_slots, E, acc);
+  dm_tier<1, NT>(sl1, st1, en1, n1, ids1, hB + (int64_t)h_base(1, n3, n2) * Bp, grp, d, G, slots,
+                 slot_bytes, n_slots, E, acc);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[t][e] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-  // the waves' h staging (16 NT rows of at most 16 dm_steps<1>() floats
-  // each) lives in s_y until the partial results take it
-  float* s_hw = &s_y[0][0][0] + w * 16 * NT * 16 * dm_steps<1>();
-  if (tier == 3)
-    dm_wave<3, NT>(lo + w * 16 * dm_steps<3>(), hi, grp, d, G, B, cap, work_slot, hB, slots,
-                   slot_bytes, n_slots, s_hw, acc);
-  else if (tier == 2)
-    dm_wave<2, NT>(lo + w * 16 * dm_steps<2>(), hi, grp, d, G, B, cap, work_slot, hB, slots,
-                   slot_bytes, n_slots, s_hw, acc);
-  else
-    dm_wave<1, NT>(lo + w * 16 * dm_steps<1>(), hi, grp, d, G, B, cap, work_slot, hB, slots,
-                   slot_bytes, n_slots, s_hw, acc);
-  __syncthreads();  // every wave's h staging is read
-  const int lane = threadIdx.x & 63, x = lane & 15, j = lane >> 4;
+    for (int i = 0; i < 4; ++i) {
+      const int er = -__shfl(E[t], 4 * j + i);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        acc[t][e][i] = ldexpf(NT == 1 ? acc[0][e][i] + acc[1][e][i] : acc[t][e][i], er);
+    }
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
     if (w / kDMRegions == pass) {
@@ -707,18 +760,23 @@ __global__ __launch_bounds__(kDMThreads) void ffn_bdm_kernel(
   }
 }
 
-static void launch_bdm(int d, int batch, int cap, hipStream_t stream, const int32_t* counts,
+// One round of workgroups, two per CU (the registers' limit), and so one set
+// of atomics per two waves of a SIMD: 512 in all, or fewer where the plan's
+// capacity has no step for them. With 512-thread workgroups 256 / 512 / 1024
+// took 13.5 / 16.1 / 19.3 us (7B, batch 8) and 41.7 / 51.1 / 63.6 (70B, 32).
+constexpr int kDMGrid = 512;
+static void launch_bdn(int d, int batch, int cap, hipStream_t stream, const int32_t* counts,
                        const int32_t* work_slot, const float* hB, const uint8_t* slots,
                        int64_t sb, int n_slots, float* y) {
-  // runs of dm_run_len<tier>() items: at most ceil(cap / R_FP16) + 2 per group
-  constexpr int R3 = dm_run_len<3>();
-  const int runs = (cap + R3 - 1) / R3 + 2;
   const int G = d >> 7;
+  const int most = (cap / kDMStep + 3 + kDMWaves - 1) / kDMWaves;
+  int per = kDMGrid > G ? kDMGrid / G : 1;
+  if (per > most) per = most;
   if (batch <= 16)
-    hipLaunchKernelGGL(ffn_bdm_kernel<1>, dim3(G * runs), dim3(kDMThreads), 0, stream, d, batch,
+    hipLaunchKernelGGL(ffn_bdn_kernel<1>, dim3(G * per), dim3(kDMThreads), 0, stream, d, batch,
                        counts, work_slot, hB, slots, sb, cap, n_slots, y);
   else
-    hipLaunchKernelGGL(ffn_bdm_kernel<2>, dim3(G * runs), dim3(kDMThreads), 0, stream, d, batch,
+    hipLaunchKernelGGL(ffn_bdn_kernel<2>, dim3(G * per), dim3(kDMThreads), 0, stream, d, batch,
                        counts, work_slot, hB, slots, sb, cap, n_slots, y);
 }
 
@@ -733,7 +791,7 @@ hipError_t launch_ffn_batch(m2c_layer* L, const uint16_t* x, int batch, const ui
   const int n_slots = L->desc.cache_slots + L->S;
   const int cap = L->cap;
   if (cap <= 0) return hipSuccess;
-  float* hB = reinterpret_cast<float*>(L->ab);  // [batch][cap rounded up to 4]
+  float* hB = reinterpret_cast<float*>(L->ab);  // h_base() says how it is laid out
   // tiles of 8 (FP16) and 16 items: at most ceil(cap/8) + 2 for any split into tiers
   const int tiles = (cap + 7) / 8 + 2;
   if (batch <= 8) {
@@ -748,7 +806,7 @@ hipError_t launch_ffn_batch(m2c_layer* L, const uint16_t* x, int batch, const ui
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  launch_bdm(d, batch, cap, stream, counts, work_slot, hB, L->slots, sb, n_slots, y);
+  launch_bdn(d, batch, cap, stream, counts, work_slot, hB, L->slots, sb, n_slots, y);
   return hipGetLastError();
 }
 

@@ -250,7 +250,9 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
       {&p_bias, with_bias ? dff * 4 : 0},
       {&p_z, mb * r * 4},
       {&p_scores, mb * dff * 4},
-      {&p_h, 4 * cap * mb * 8},
+      // FFN partial dot products; the batched FFN's h values (32 rows, every
+      // tier's items from a multiple of 32)
+      {&p_h, 4 * cap * mb * 8 > (cap + 128) * 128 || mb == 1 ? 4 * cap * mb * 8 : (cap + 128) * 128},
       {&p_ypart, (int64_t)ng * mb * d * 4},
       {&p_slot_of, (L->pools ? 3 : 1) * dff * 4},
       {&p_slot_key, C * 4},
