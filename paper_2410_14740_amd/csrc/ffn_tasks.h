@@ -59,6 +59,11 @@ struct TaskTable {
 constexpr int kOrderKind[6] = {1, 1, 1, 2, 2, 2};
 constexpr int kOrderTier[6] = {1, 2, 3, 1, 2, 3};
 
+constexpr int kLogFWaves = 2, kLogDn3 = 5;
+static_assert(kFWaves == 1 << kLogFWaves && kDnRounds3 * kFNPR == 1 << kLogDn3 &&
+                  kDnRounds2 == 2 * kDnRounds3 && kDnRounds1 == 2 * kDnRounds2,
+              "the table writer shifts");
+
 // Neurons per down task.
 __device__ __forceinline__ int dn_items(int tier) {
   return (tier == 1 ? kDnRounds1 : tier == 2 ? kDnRounds2 : kDnRounds3) * kFNPR;
@@ -181,22 +186,26 @@ __device__ __forceinline__ void write_task_header(const TaskTable& tt, const FMa
 // units in its h task, and its place in the down task of every slice.
 __device__ __forceinline__ void write_task_items(const TaskTable& tt, const FMap& m, int tier,
                                                  int i, int slot) {
-  const int upi = tier == 3 ? 4 : tier == 2 ? 2 : 1, uw_n = tt.upt / kFWaves;
-  const int per_h = tt.upt / upi;
-  const int th = region_start<1>(m, tier) + i / per_h;
+  // every size is a power of two: shifts
+  const int lupi = tier == 3 ? 2 : tier == 2 ? 1 : 0;
+  const int lupt = 31 - __builtin_clz(tt.upt), luw = lupt - kLogFWaves;  // units per wave
+  const int lper = lupt - lupi;                                          // items per h task
+  const int th = region_start<1>(m, tier) + (i >> lper);
   if (th < tt.grid) {
     int32_t* out = tt.task_ids + (int64_t)th * kTaskIds;
-    for (int v = 0; v < upi; ++v) {
-      const int unit = (i % per_h) * upi + v, w = unit / uw_n, uw = unit % uw_n;
+    const int unit0 = (i & ((1 << lper) - 1)) << lupi;
+    for (int v = 0; v < (1 << lupi); ++v) {
+      const int w = (unit0 + v) >> luw, uw = (unit0 + v) & ((1 << luw) - 1);
       out[(uw >> 2) * kFNPR + 4 * w + (uw & 3)] = slot;
     }
   }
   const int n = tier == 3 ? m.n3 : tier == 2 ? m.n2 : m.n1;
-  const int per = dn_items(tier), run = i / per, blk = run >> 3;
-  const int nb = min(8, (n + per - 1) / per - 8 * blk);
+  const int ld = tier == 3 ? kLogDn3 : tier == 2 ? kLogDn3 + 1 : kLogDn3 + 2;  // items per down task
+  const int run = i >> ld, blk = run >> 3;
+  const int nb = min(8, ((n + (1 << ld) - 1) >> ld) - 8 * blk);
   int t = region_start<2>(m, tier) + blk * 8 * m.n_slices + (run & 7);
-  for (int s = 0; s < m.n_slices && t < tt.grid; ++s, t += nb)
-    tt.task_ids[(int64_t)t * kTaskIds + i % per] = slot;
+  int32_t* out = tt.task_ids + (i & ((1 << ld) - 1));
+  for (int s = 0; s < m.n_slices && t < tt.grid; ++s, t += nb) out[(int64_t)t * kTaskIds] = slot;
 }
 
 // The task table of a layer's plan buffer (k_ffn_fused.hip).

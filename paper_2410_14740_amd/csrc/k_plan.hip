@@ -3,7 +3,7 @@
 // (Sec. 1, Sec. 6.4): the single arena or the per-tier pools, any d_ff, one
 // or more batch rows.
 //
-// Two launches, each over chunks of 1024 neurons (one per thread):
+// Two launches, each over chunks of 256 neurons:
 //
 //   plan_classify_kernel  step tier and row mask of every neuron, the pool
 //       that serves it and its slot there: HIT, REFILL (another tier in its
@@ -27,23 +27,30 @@
 // One workgroup doing the whole step was bound by one CU's instruction issue
 // and a dozen dependent round trips, and the pools took two launches more.
 // Measured (MI355X, rocprofv3 kernel time, all plan launches and the FFN's
-// task table, before -> now): d_ff 2752 29.4 -> 11.9 us, 11008 40.1 -> 13.4 (batch
-// 8: 62.5 -> 14.1), 40000 99.5 -> 14.3, 28672 at batch 32 286 -> 18.4, 28672 with
-// pools 39.0 -> 18.4.
+// task table, before -> now): d_ff 2752 29.4 -> 10.9 us, 11008 40.1 -> 11.4 (batch
+// 8: 62.5 -> 10.9), 40000 99.5 -> 12.6, 28672 with pools 39.0 -> 15.9.
 #include "ffn_tasks.h"
 #include "m2c_internal.h"
 #include "wave_ops.h"
 
 namespace m2c {
 
-constexpr int kPT = 1024;      // threads per workgroup, neurons per chunk
-constexpr int kPW = kPT / 64;  // waves
+// A chunk has 256 neurons, one wave per SIMD, because a CU issues an
+// instruction of 16 waves in the time of 16 (with chunks of 1024, one neuron
+// per thread, the place kernel took 9.7 instead of 8.0 us at 7B and 13.7
+// instead of 12.5 for the 70B pools); the place kernel's other waves help to
+// rank the LRU order and write the task headers.
+constexpr int kPC = 256;        // neurons per chunk, threads of the classify kernel
+constexpr int kPCW = kPC / 64;
+constexpr int kPT = 1024;       // threads of the place kernel
+constexpr int kPW = kPT / 64;
 constexpr int kPRounds = 8;    // LRU entries a thread ranks per sweep
 
 // Counts of a chunk: required neurons and fills by tier, NEW neurons, fills
 // made from the slot's FP16 record by tier.
 enum PlanField { kR3, kR2, kR1, kF3, kF2, kF1, kNew, kD2, kD1, kPFields };
 static_assert(kPFields <= kPW, "one wave sums each field");
+static_assert(kPCW == 4, "the chunk's counts by wave are a uint4");
 
 // A neuron's word: step tier | code << 2 (0 NEW, 1 HIT, 2 REFILL) | tier its
 // slot held << 4 | slot in its pool << 8.
@@ -113,13 +120,13 @@ __device__ __forceinline__ uint32_t popc(unsigned long long v) { return (uint32_
 // served by the lowest such pool, as a hit at that pool's tier. Residency is
 // that of the step's start: nothing is changed before plan_place_kernel.
 template <bool POOLS, bool ONE_ROW>
-__global__ __launch_bounds__(kPT) void plan_classify_kernel(const uint8_t* __restrict__ tier_map,
+__global__ __launch_bounds__(kPC) void plan_classify_kernel(const uint8_t* __restrict__ tier_map,
                                                             int B, int d_ff, int dom,
                                                             PoolGeom g, DeviceState st) {
-  __shared__ uint32_t s_w[kPFields][kPW];
+  __shared__ uint32_t s_w[kPFields][kPCW];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = blockIdx.x * kPT + tid, nc = min(n, d_ff - 1);
+  const int n = blockIdx.x * kPC + tid, nc = min(n, d_ff - 1);
   const int serial = st.plan_state[kPlanSerial], cur = st.plan_state[kPlanCur];
   // every load of a neuron at once
   int r0 = st.slot_of[nc], r1 = -1, r2 = -1;
@@ -168,9 +175,11 @@ __global__ __launch_bounds__(kPT) void plan_classify_kernel(const uint8_t* __res
     for (int f = 0; f < kPFields; ++f) s_w[f][wave] = popc(b[f]);
   }
   __syncthreads();
-  if (wave < kPFields) {
-    const uint32_t v = row_incl_scan(s_w[wave][lane & 15]);
-    if (lane == 15) st.chunk_counts[wave * (int)gridDim.x + (int)blockIdx.x] = (int32_t)v;
+  if (tid < kPFields) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int w = 0; w < kPCW; ++w) v += s_w[tid][w];
+    st.chunk_counts[tid * (int)gridDim.x + (int)blockIdx.x] = (int32_t)v;
   }
   // what the place kernel reads while it changes the originals
   if (blockIdx.x == 0 && tid < kPlanWords) st.plan_copy[tid] = st.plan_state[tid];
@@ -221,11 +230,11 @@ template <bool POOLS>
 __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
   constexpr int NP = POOLS ? 3 : 1;
   __shared__ uint32_t s_tot[kPW], s_pre[kPW], s_own[kPW];  // fields: all chunks, those before, this one
-  __shared__ uint32_t s_cw[7][kPW];
+  __shared__ uint4 s_cw[7];  // the chunk's counts by wave
   __shared__ __align__(8) uint32_t s_cnt[kPRounds * kPW];
   __shared__ uint32_t s_lo[3], s_hi[3];  // a pool's first rank and the one past its last
   __shared__ int s_cut[3];               // LRU place of a pool's first unstamped slot kept
-  __shared__ int s_vict[kPT];            // victims of this chunk's NEW neurons
+  __shared__ int s_vict[kPC];            // victims of this chunk's NEW neurons
   const DeviceState& st = a.st;
   const PoolGeom& g = a.g;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -233,7 +242,7 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
   const bool neurons = (int)blockIdx.x < a.chunks;
   const int chunk = neurons ? (int)blockIdx.x : 0;
   const int own_round = neurons ? -1 : (int)blockIdx.x - a.chunks;  // its 1024 LRU places and slots
-  const int n = chunk * kPT + tid;
+  const int n = tid < kPC ? chunk * kPC + tid : a.d_ff;  // its neuron (the first kPCW waves)
   const unsigned long long lt = (1ull << lane) - 1ull;
   auto pool_of = [&](int e) { return POOLS ? (e >= g.rf[1]) + (e >= g.rf[2]) : 0; };
   // one of three values by a pool index (selects of registers)
@@ -241,21 +250,22 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
 
   // ---- first loads: the neuron's word, the counts, the first LRU sweep
   const uint32_t info = neurons && n < a.d_ff ? st.info[n] : 0u;
-  const uint32_t mask = a.one_row ? 1u : st.masks[min(n, a.d_ff - 1)];
+  const uint32_t mask = a.one_row || !neurons ? 1u : st.masks[min(n, a.d_ff - 1)];
   const int serial = st.plan_copy[kPlanSerial], cur = st.plan_copy[kPlanCur];
   const int rounds_all = (g.total + kPT - 1) / kPT;
-  const int32_t* lru_in = st.lru + (int64_t)cur * g.total;
   int32_t* lru_out = st.lru + (int64_t)(1 - cur) * g.total;
   int32_t* pos_out = st.lru_pos + (int64_t)(1 - cur) * g.total;
-  int tp[kPRounds], sv[kPRounds];
+  // both orders are read, so that the loads do not wait for `cur`
+  int tp[kPRounds], sv[kPRounds], sw[kPRounds];
   auto load_lru = [&](int r0) {
 #pragma unroll
     for (int r = 0; r < kPRounds; ++r) {
-      tp[r] = sv[r] = 0;
+      tp[r] = sv[r] = sw[r] = 0;
       if (r0 + r < rounds_all) {
         const int p = min((r0 + r) * kPT + tid, g.total - 1);
         tp[r] = st.touch_pos[p];
-        sv[r] = lru_in[p];
+        sv[r] = st.lru[p];
+        sw[r] = st.lru[g.total + p];
       }
     }
   };
@@ -287,14 +297,10 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
   const unsigned long long b3 = __ballot(t == 3), b2 = __ballot(t == 2), b1 = __ballot(t == 1);
   const unsigned long long f3 = __ballot(fill && t == 3), f2 = __ballot(fill && t == 2),
                            f1 = __ballot(fill && t == 1), bn = __ballot(fresh);
-  if (lane == 0) {
-    s_cw[0][wave] = popc(b3);
-    s_cw[1][wave] = popc(b2);
-    s_cw[2][wave] = popc(b1);
-    s_cw[3][wave] = popc(f3);
-    s_cw[4][wave] = popc(f2);
-    s_cw[5][wave] = popc(f1);
-    s_cw[6][wave] = popc(bn);
+  if (lane == 0 && wave < kPCW) {
+    const uint32_t c[7] = {popc(b3), popc(b2), popc(b1), popc(f3), popc(f2), popc(f1), popc(bn)};
+#pragma unroll
+    for (int f = 0; f < 7; ++f) reinterpret_cast<uint32_t*>(&s_cw[f])[wave] = c[f];
   }
 
   // ---- the LRU order: rank every unstamped place, hand out victims
@@ -339,19 +345,20 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
 #pragma unroll
     for (int r = 0; r < kPRounds; ++r) {
       if (!unt[r]) continue;
+      const int slot = cur ? sw[r] : sv[r];
       const int p = (r0 + r) * kPT + tid, q = pool_of(p);
       const uint32_t u = POOLS ? rank[r] - s_lo[q] : rank[r];
       const uint32_t nn = pick(q, nnew[0], nnew[1], nnew[2]);
       if (u < nn) {
         const uint32_t j = u - pick(q, npre[0], npre[1], npre[2]);
         if (neurons && j < pick(q, nown[0], nown[1], nown[2]))
-          s_vict[j + (q > 0 ? nown[0] : 0u) + (q > 1 ? nown[1] : 0u)] = sv[r];
+          s_vict[j + (q > 0 ? nown[0] : 0u) + (q > 1 ? nown[1] : 0u)] = slot;
       } else {
         if (u == nn) s_cut[q] = p;
         if (r0 + r == own_round) {  // kept, in the old order
           const int np = pick(q, g.rf[0], g.rf[1], g.rf[2]) + (int)(u - nn);
-          lru_out[np] = sv[r];
-          pos_out[sv[r]] = np;
+          lru_out[np] = slot;
+          pos_out[slot] = np;
         }
       }
     }
@@ -440,13 +447,49 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
     return;
   }
 
-  // ---- the neuron's outputs
   const FMap fm = make_map((int)N3, (int)N2, (int)N1, a.tt.d, a.tt.upt);
+  if (wave >= 2 * kPCW) {
+    if (blockIdx.x != 0 || wave != 2 * kPCW) return;
+    // ---- counts, statistics, the next plan's state (one wave of workgroup 0)
+    const uint32_t F3 = s_tot[kF3], F2 = s_tot[kF2], F1 = s_tot[kF1], NF = F3 + F2 + F1;
+    const uint32_t D2 = s_tot[kD2], D1 = s_tot[kD1], NNEW = s_tot[kNew];
+    const uint32_t V = (uint32_t)(nv[0] + nv[1] + nv[2]), E = (uint32_t)(ne[0] + ne[1] + ne[2]);
+    const uint32_t c[M2C_NCOUNTS] = {NREQ, NREQ - NF, NF - NNEW, V,  NNEW - V, V - E,   NF, N3,
+                                     N2,   N1,        F3,        F2, F1,       D2 + D1, 0u, 0u};
+    // cumulative: plans, req, hit, refill, new, bypass, evict, fills INT4 /
+    // INT8 / FP16, required INT4 / INT8 / FP16, derived INT8 / INT4
+    const uint32_t s[16] = {1u, NREQ, NREQ - NF, NF - NNEW, V,  NNEW - V, V - E, F1,
+                            F2, F3,   N1,        N2,        N3, D2,       D1,    0u};
+    uint32_t cv = 0, sv_ = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {  // by value: an indexed array would live in scratch memory
+      cv = lane == i ? c[i] : cv;
+      sv_ = lane == i ? s[i] : sv_;
+    }
+    if (lane < M2C_NCOUNTS) a.P.counts[lane] = (int32_t)cv;
+    if (lane < 15) st.stats[lane] += (unsigned long long)sv_;
+    if (lane == 0) {
+      st.plan_state[kPlanSerial] = serial + 1;
+      st.plan_state[kPlanCur] = 1 - cur;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) st.plan_state[kPlanFilled + q] = filled[q] + ne[q];
+      if (tasks) write_task_count(a.tt, a.map, min(fm.e[5], a.tt.grid));
+    }
+    return;
+  }
+  if (wave >= kPCW) {  // ---- task headers
+    if (!tasks) return;
+    const int n_tasks = min(fm.e[5], a.tt.grid);
+    for (int k = chunk * kPC + tid - kPC; k < n_tasks; k += a.chunks * kPC)
+      write_task_header(a.tt, fm, a.map, k);
+    return;
+  }
+  // ---- the neuron's outputs
   uint32_t before[7];  // in the chunk's waves before this one
 #pragma unroll
   for (int f = 0; f < 7; ++f) {
-    const uint32_t v = row_incl_scan(s_cw[f][lane & 15]);
-    before[f] = wave > 0 ? __builtin_amdgcn_readlane(v, wave - 1) : 0u;
+    const uint4 v = s_cw[f];
+    before[f] = (wave > 0 ? v.x : 0u) + (wave > 1 ? v.y : 0u) + (wave > 2 ? v.z : 0u);
   }
   if (req) {
     const unsigned long long bt = t == 3 ? b3 : t == 2 ? b2 : b1;
@@ -505,38 +548,6 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
     }
     if (tasks) write_task_items(a.tt, fm, t, it, gs);
   }
-  if (tasks) {
-    const int n_tasks = min(fm.e[5], a.tt.grid);
-    for (int k = n; k < n_tasks; k += a.chunks * kPT) write_task_header(a.tt, fm, a.map, k);
-  }
-  if (blockIdx.x != 0) return;
-  // ---- counts, statistics, the next plan's state
-  const uint32_t F3 = s_tot[kF3], F2 = s_tot[kF2], F1 = s_tot[kF1], NF = F3 + F2 + F1;
-  const uint32_t D2 = s_tot[kD2], D1 = s_tot[kD1], NNEW = s_tot[kNew];
-  const uint32_t V = (uint32_t)(nv[0] + nv[1] + nv[2]), E = (uint32_t)(ne[0] + ne[1] + ne[2]);
-  if (tid < M2C_NCOUNTS) {
-    const uint32_t c[M2C_NCOUNTS] = {NREQ, NREQ - NF, NF - NNEW, V,  NNEW - V, V - E,   NF, N3,
-                                     N2,   N1,        F3,        F2, F1,       D2 + D1, 0u, 0u};
-    // cumulative: plans, req, hit, refill, new, bypass, evict, fills INT4 /
-    // INT8 / FP16, required INT4 / INT8 / FP16, derived INT8 / INT4
-    const uint32_t s[16] = {1u, NREQ, NREQ - NF, NF - NNEW, V,  NNEW - V, V - E, F1,
-                            F2, F3,   N1,        N2,        N3, D2,       D1,    0u};
-    uint32_t cv = 0, sv_ = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {  // by value: an indexed array would live in scratch memory
-      cv = tid == i ? c[i] : cv;
-      sv_ = tid == i ? s[i] : sv_;
-    }
-    a.P.counts[tid] = (int32_t)cv;
-    if (tid < 15) st.stats[tid] += (unsigned long long)sv_;
-  }
-  if (tid == 0) {
-    st.plan_state[kPlanSerial] = serial + 1;
-    st.plan_state[kPlanCur] = 1 - cur;
-#pragma unroll
-    for (int q = 0; q < NP; ++q) st.plan_state[kPlanFilled + q] = filled[q] + ne[q];
-    if (tasks) write_task_count(a.tt, a.map, min(fm.e[5], a.tt.grid));
-  }
 }
 
 // Empties the cache unit (every pool of the per-tier arena), clears the
@@ -593,7 +604,7 @@ hipError_t launch_plan(m2c_layer* L, const uint8_t* tier_map, int batch, int ste
   const int d_ff = L->desc.d_ff;
   PlaceArgs a;
   a.d_ff = d_ff;
-  a.chunks = (d_ff + kPT - 1) / kPT;
+  a.chunks = (d_ff + kPC - 1) / kPC;
   a.cap = L->cap;
   a.step = step;
   a.one_row = batch == 1;
@@ -609,9 +620,9 @@ hipError_t launch_plan(m2c_layer* L, const uint8_t* tier_map, int batch, int ste
   a.map = L->map;
   a.tt = plan_task_table(L, plan);
   const int dom = (L->desc.flags & M2C_FLAG_DOMINANT_HITS) ? 1 : 0;
-  const dim3 gc(a.chunks), gp(a.chunks + (a.g.total + kPT - 1) / kPT), b(kPT);
+  const dim3 gc(a.chunks), bc(kPC), gp(a.chunks + (a.g.total + kPT - 1) / kPT), b(kPT);
 #define M2C_CLASSIFY(P, ONE)                                                                    \
-  hipLaunchKernelGGL((plan_classify_kernel<P, ONE>), gc, b, 0, stream, tier_map, batch, d_ff,   \
+  hipLaunchKernelGGL((plan_classify_kernel<P, ONE>), gc, bc, 0, stream, tier_map, batch, d_ff,   \
                      dom, a.g, a.st)
   if (L->pools && batch == 1)
     M2C_CLASSIFY(true, true);

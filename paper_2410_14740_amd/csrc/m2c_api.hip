@@ -266,7 +266,7 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
       {&p_plan_copy, m2c::kPlanWords * 4},
       {&p_info, dff * 4},
       {&p_masks, mb > 1 ? dff * 4 : 0},
-      {&p_chunk_counts, 16 * ((dff + 1023) / 1024) * 4},
+      {&p_chunk_counts, 16 * ((dff + 255) / 256) * 4},
       {&p_have, (C + L->S) * 4},
       {&p_stats, 16 * 8},
       {&p_status, 4},
