@@ -962,7 +962,7 @@ def main():
         return {"bound": "hbm", "achieved": g["achieved_GBps"], "peak": PEAK_HBM_GBPS,
                 "unit": "GB/s", "frac": g["achieved_GBps"] / PEAK_HBM_GBPS,
                 "traffic": traffic(name) if W.WORKLOADS[name].batch == 1 else None,
-                "kernel": ("m2c_sparse_ffn (ffn_bh_kernel + ffn_bdm_kernel)"
+                "kernel": ("m2c_sparse_ffn (ffn_bh_kernel + ffn_bdn_kernel)"
                            if W.WORKLOADS[name].batch > 1 else "m2c_sparse_ffn (ffn_fused_kernel)"),
                 "workload": f"{name} layer shape, {layers_cycled} layers cycled",
                 "bytes_per_launch": g["bytes_per_launch"], "us_per_launch": g["us_avg"]}
