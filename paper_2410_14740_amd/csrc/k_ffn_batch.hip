@@ -10,7 +10,8 @@
 // gathered (2|R| x d) by (d x B) product, so it runs on the matrix cores:
 //
 //   ffn_bh_kernel   a workgroup takes a tile of 16 neurons of one tier (8 for
-//                   FP16, padded with the zero slot); its 8
+//                   FP16, padded with the zero slot; twice that above 16
+//                   rows on large unions); its 8
 //                   waves split d by quantization group (group g to wave
 //                   g % 8). For each group a wave issues four
 //                   v_mfma_f32_16x16x32_f16 steps per row kind over the 128
@@ -89,29 +90,40 @@ __device__ __forceinline__ int h_base(int tier, int n3, int n2) {
 // Tile b: up to 16 consecutive work items of one tier. An FP16 tile takes 8
 // items (the MFMA rows past them read the zero slot), so that it carries about
 // as many record bytes as an INT8 tile of 16 and the workgroups finish
-// together instead of the FP16 tiles trailing.
-__device__ __forceinline__ void bh_tile(int b, int n3, int n2, int n1, int& tier, int& item0,
-                                        int& nitems) {
-  const int t3 = (n3 + 7) >> 3, t2 = (n2 + 15) >> 4, t1 = (n1 + 15) >> 4;
+// together instead of the FP16 tiles trailing. Wide tiles are twice that.
+__device__ __forceinline__ void bh_tile(int b, int n3, int n2, int n1, int wide, int& tier,
+                                        int& item0, int& nitems) {
+  const int l3 = 3 + wide, l = 4 + wide;  // log2 of the tile's items
+  const int t3 = (n3 + (1 << l3) - 1) >> l3;
+  const int t2 = (n2 + (1 << l) - 1) >> l, t1 = (n1 + (1 << l) - 1) >> l;
   if (b < t3) {
     tier = 3;
-    item0 = 8 * b;
-    nitems = min(8, n3 - item0);
+    item0 = b << l3;
+    nitems = min(1 << l3, n3 - item0);
   } else if (b < t3 + t2) {
     tier = 2;
-    item0 = 16 * (b - t3);
-    nitems = min(16, n2 - item0);
+    item0 = (b - t3) << l;
+    nitems = min(1 << l, n2 - item0);
     item0 += n3;
   } else if (b < t3 + t2 + t1) {
     tier = 1;
-    item0 = 16 * (b - t3 - t2);
-    nitems = min(16, n1 - item0);
+    item0 = (b - t3 - t2) << l;
+    nitems = min(1 << l, n1 - item0);
     item0 += n3 + n2;
   } else {
     tier = 0;
     item0 = nitems = 0;
   }
 }
+
+// Above 16 rows a workgroup holds a CU alone (its registers), and each reads
+// all of x (32 rows: as many bytes as 2 to 4 tiles' INT8 or INT4 codes). Wide
+// tiles halve those reads and the rounds of workgroups; they are taken when the
+// tiles of 16 are more than one per CU. Measured (MI355X, both launches of a call,
+// tiles of 16 -> wide): 70B shape at 32 rows (935 tiles of 16) 121.5 -> 105.2 us,
+// 13B (640) 63.1 -> 61.5, d 4096 (341) 38.0 -> 35.8, d 12288 (269) 67.9 -> 63.5;
+// even where the wide ones just miss one round (7B at 17 rows, 529: 46.0, 46.7).
+constexpr int kBHWideTiles = 256;
 
 // One group (128 columns) of a tile on the matrix cores, as four
 // v_mfma_f32_16x16x32_f16 steps per row kind (gate, up). Lane (row r, lane
@@ -173,19 +185,21 @@ struct GroupA {
 // The global loads of one group: x rows 4 q + j (q < NXQ; 16-byte chunk
 // col; rows past the batch re-read the last row, and are stored as zeros)
 // and the records. Every load is unconditional.
-template <int TIER, int NXQ>
+template <int TIER, int MT, int NXQ>
 struct BhLoads {
-  GroupA<TIER> A;
+  GroupA<TIER> A[MT];
   uint4 xr[NXQ];
-  __device__ __forceinline__ void issue(const uint16_t* x, const uint8_t* rec, int d, int B,
-                                        int grp, int lane) {
+  __device__ __forceinline__ void issue_x(const uint16_t* x, int d, int B, int grp, int lane) {
     const int j = lane >> 4, col = lane & 15;
 #pragma unroll
     for (int q = 0; q < NXQ; ++q) {
       const int row = min(4 * q + j, B - 1);
       xr[q] = *reinterpret_cast<const uint4*>(x + (int64_t)row * d + 128 * grp + 8 * col);
     }
-    A.load(rec, d, grp, j);
+  }
+  __device__ __forceinline__ void issue_a(const uint8_t* const* rec, int d, int grp, int lane) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m) A[m].load(rec[m], d, grp, lane >> 4);
   }
   // the x rows into the wave's LDS copy (the asm makes the values used
   // whatever the row, so that no load of a row past the batch moves under
@@ -204,70 +218,92 @@ struct BhLoads {
   }
 };
 
-// The arithmetic of one group, x staged in s_xw.
-template <int TIER, int NT>
-__device__ __forceinline__ void bh_compute(const GroupA<TIER>& A, const uint16_t* s_xw,
+// The arithmetic of one group, x staged in s_xw: MT tiles of 16 neurons.
+template <int TIER, int MT, int NT, int MA>
+__device__ __forceinline__ void bh_compute(const GroupA<TIER> (&A)[MT], const uint16_t* s_xw,
                                            const uint16_t* s_sc, int G, int grp, int lane,
-                                           float4v (&acc_g)[NT], float4v (&acc_u)[NT]) {
+                                           float4v (&acc_g)[MA][NT], float4v (&acc_u)[MA][NT]) {
   const int j = lane >> 4, col = lane & 15;
-  float4v tg[NT], tu[NT];
+  // one tile of neurons after the other: both at once read x from LDS once, but
+  // their products do not fit the registers
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    tg[t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-    tu[t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const half8v ag = GroupA<TIER>::step(A.g, s), au = GroupA<TIER>::step(A.u, s);
+  for (int m = 0; m < MT; ++m) {
+    float4v tg[NT], tu[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const half8v bx = *reinterpret_cast<const half8v*>(s_xw + (16 * t + col) * kBXRow +
-                                                          bh_xcol<TIER>(j, s));
-      tg[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ag, bx, tg[t], 0, 0, 0);
-      tu[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(au, bx, tu[t], 0, 0, 0);
+      tg[t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+      tu[t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
     }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const half8v ag = GroupA<TIER>::step(A[m].g, s), au = GroupA<TIER>::step(A[m].u, s);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const half8v bx = *reinterpret_cast<const half8v*>(s_xw + (16 * t + col) * kBXRow +
+                                                            bh_xcol<TIER>(j, s));
+        tg[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ag, bx, tg[t], 0, 0, 0);
+        tu[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(au, bx, tu[t], 0, 0, 0);
+      }
+    }
+    // rows 4j + i of the tile's result: scale each by its neuron's group scale
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float sg = 1.0f, su = 1.0f;
+      if (TIER != 3) {
+        sg = h2f(s_sc[(16 * m + 4 * j + i) * bh_scale_row(G) + grp]);
+        su = h2f(s_sc[(16 * m + 4 * j + i) * bh_scale_row(G) + G + grp]);
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        acc_g[m][t][i] = fmaf(sg, tg[t][i], acc_g[m][t][i]);
+        acc_u[m][t][i] = fmaf(su, tu[t][i], acc_u[m][t][i]);
+      }
+    }
+    if (m + 1 < MT) __builtin_amdgcn_sched_barrier(0);
   }
-  // rows 4j + i of the result: scale each by its neuron's group scale
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float sg = 1.0f, su = 1.0f;
-    if (TIER != 3) {
-      sg = h2f(s_sc[(4 * j + i) * bh_scale_row(G) + grp]);
-      su = h2f(s_sc[(4 * j + i) * bh_scale_row(G) + G + grp]);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      acc_g[t][i] = fmaf(sg, tg[t][i], acc_g[t][i]);
-      acc_u[t][i] = fmaf(su, tu[t][i], acc_u[t][i]);
-    }
+}
+
+// The loads of the next group, and the current one's x rows into LDS. With
+// wide tiles the next x rows are loaded only when the current ones have left
+// their registers (both sets do not fit).
+template <int TIER, int MT, int NXQ>
+__device__ __forceinline__ void bh_next(BhLoads<TIER, MT, NXQ>& next, BhLoads<TIER, MT, NXQ>& cur,
+                                        const uint16_t* x, const uint8_t* const* rec, int d, int B,
+                                        int grp, uint16_t* s_xw, int lane) {
+  if (MT == 1) next.issue_x(x, d, B, grp, lane);
+  next.issue_a(rec, d, grp, lane);
+  cur.stage(s_xw, B, lane);
+  if (MT > 1) {
+    __builtin_amdgcn_sched_barrier(0);
+    next.issue_x(x, d, B, grp, lane);
   }
 }
 
 // NT: 16-column tiles of the batch (1 for B <= 16, 2 for B <= 32); NXQ: x
-// loads per lane and group (4 NXQ >= B). s_xw: this wave's x rows (16 NT of
+// loads per lane and group (4 NXQ >= B); MT: 16-row tiles of neurons. s_xw: this wave's x rows (16 NT of
 // kBXRow halves; rows from 4 NXQ on are zero from the start). s_sc: the
-// tile's gate and up group scales, [16][bh_scale_row(G)] halves. The wave's
+// tile's gate and up group scales, [16 MT][bh_scale_row(G)] halves. The wave's
 // groups are w, w + 8, ...; the loads of the next one go out before the
 // current one's arithmetic (past the last group the prefetch re-reads the
 // current one, which keeps every load unconditional).
-template <int TIER, int NT, int NXQ>
+template <int TIER, int MT, int NT, int NXQ, int MA>
 __device__ __forceinline__ void bh_tier(int lane, int w, int d, int G, int B, const uint16_t* x,
-                                        const uint8_t* rec, uint16_t* s_xw, const uint16_t* s_sc,
-                                        float4v (&acc_g)[NT], float4v (&acc_u)[NT]) {
+                                        const uint8_t* const (&rec)[MA], uint16_t* s_xw,
+                                        const uint16_t* s_sc, float4v (&acc_g)[MA][NT],
+                                        float4v (&acc_u)[MA][NT]) {
   int grp = w;
   if (grp >= G) return;  // wave-uniform
-  BhLoads<TIER, NXQ> L0, L1;
-  L0.issue(x, rec, d, B, grp, lane);
+  BhLoads<TIER, MT, NXQ> L0, L1;
+  L0.issue_x(x, d, B, grp, lane);
+  L0.issue_a(rec, d, grp, lane);
   for (;;) {
     const int g1 = grp + kBHWaves;
-    L1.issue(x, rec, d, B, g1 < G ? g1 : grp, lane);
-    L0.stage(s_xw, B, lane);
-    bh_compute<TIER, NT>(L0.A, s_xw, s_sc, G, grp, lane, acc_g, acc_u);
+    bh_next(L1, L0, x, rec, d, B, g1 < G ? g1 : grp, s_xw, lane);
+    bh_compute<TIER, MT, NT>(L0.A, s_xw, s_sc, G, grp, lane, acc_g, acc_u);
     if (g1 >= G) break;
     const int g2 = g1 + kBHWaves;
-    L0.issue(x, rec, d, B, g2 < G ? g2 : g1, lane);
-    L1.stage(s_xw, B, lane);
-    bh_compute<TIER, NT>(L1.A, s_xw, s_sc, G, g1, lane, acc_g, acc_u);
+    bh_next(L0, L1, x, rec, d, B, g2 < G ? g2 : g1, s_xw, lane);
+    bh_compute<TIER, MT, NT>(L1.A, s_xw, s_sc, G, g1, lane, acc_g, acc_u);
     if (g2 >= G) break;
     grp = g2;
   }
@@ -275,12 +311,14 @@ __device__ __forceinline__ void bh_tier(int lane, int w, int d, int G, int B, co
 
 // LDS of ffn_bh_kernel: the waves' x rows, then (after the main loop, over
 // the same bytes) the waves' partial results; the tile's gate and up scales
-// follow, [16][bh_scale_row(G)] halves (rows padded to 16 bytes; G <= 128).
+// follow, [16 MA][bh_scale_row(G)] halves (rows padded to 16 bytes; G <= 128).
+// MA: the most 16-row tiles of neurons of a workgroup (wide tiles from 17 rows).
 template <int NT>
 __host__ __device__ constexpr int bh_lds_words() {
-  return (kBHWaves * 16 * NT * kBXRow * 2 + 16 * bh_scale_row(128) * 2) / 16;
+  return (kBHWaves * 16 * NT * kBXRow * 2 + 16 * NT * bh_scale_row(128) * 2) / 16;
 }
 static_assert(kBHWaves * 2 * 16 * 16 * 4 <= kBHWaves * 16 * kBXRow * 2, "partials fit over the x rows");
+static_assert(kBHWaves * 2 * 32 * 32 * 4 <= kBHWaves * 32 * kBXRow * 2, "partials fit over the x rows");
 
 template <int NT, int NXQ>
 __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
@@ -289,11 +327,13 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
     const uint8_t* __restrict__ slots, int64_t slot_bytes, int cap, int n_slots,
     float* __restrict__ hB) {
   __shared__ uint4 bh_lds[bh_lds_words<NT>()];
-  __shared__ uint32_t s_mask[16];
+  constexpr int MA = NT;
+  __shared__ uint32_t s_mask[16 * MA];
   int n3, n2, n1;
   work_counts(counts, cap, n3, n2, n1);
   int tier, item0, nitems;
-  bh_tile(blockIdx.x, n3, n2, n1, tier, item0, nitems);
+  const int wide = MA == 2 && ((n3 + 7) >> 3) + ((n2 + 15) >> 4) + ((n1 + 15) >> 4) > kBHWideTiles;
+  bh_tile(blockIdx.x, n3, n2, n1, wide, tier, item0, nitems);
   if (nitems <= 0) return;  // workgroup-uniform
   const int G = d >> 7;
   const int lane = threadIdx.x & 63;
@@ -305,25 +345,31 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
   // plan's spare work_slot entries past the list), which do not queue behind
   // other workgroups' vector loads; each lane then picks the ids it needs with
   // branch-free masks.
-  int u[16];
+  int u[16 * MA];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
+  for (int k = 0; k < 16 * MA; ++k) {
     const int s = __builtin_amdgcn_readfirstlane(work_slot[item0 + k]);
     u[k] = k < nitems && s >= 0 && s < n_slots ? s : n_slots;  // zero slot for padding
   }
-  int my_slot = 0;
+  int my_slot[MA];
+  uint32_t my_mask[MA];  // stored after the main loop
+  const uint8_t* rec[MA];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) my_slot |= u[k] & -((lane & 15) == k);
-  const uint32_t my_mask = work_mask[min(item0 + (lane & 15), cap - 1)];  // stored after the main loop
-  const uint8_t* rec = slots + (int64_t)my_slot * slot_bytes;
+  for (int m = 0; m < MA; ++m) {
+    my_slot[m] = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) my_slot[m] |= u[16 * m + k] & -((lane & 15) == k);
+    my_mask[m] = work_mask[min(item0 + 16 * m + (lane & 15), cap - 1)];
+    rec[m] = slots + (int64_t)my_slot[m] * slot_bytes;
+  }
   // the tile's gate and up scales (4 G contiguous bytes per record) into LDS
   if (tier != 3) {
     const int cpr = bh_scale_row(G) / 8;  // 16-byte chunks per row (the last may pass 4 G bytes)
-    const int r = threadIdx.x / cpr, c = threadIdx.x - r * cpr;
-    if (r < 16) {
+    for (int e = threadIdx.x; e < (16 << wide) * cpr; e += kBHThreads) {
+      const int r = e / cpr, c = e - r * cpr;
       int sr = 0;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) sr |= u[k] & -(r == k);
+      for (int k = 0; k < 16 * MA; ++k) sr |= u[k] & -(r == k);
       const int64_t sbase = tier == 1 ? 3 * (int64_t)(d >> 1) : 3 * (int64_t)d;
       reinterpret_cast<uint4*>(s_sc)[r * cpr + c] =
           *reinterpret_cast<const uint4*>(slots + (int64_t)sr * slot_bytes + sbase + 16 * c);
@@ -333,44 +379,59 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
   for (int e = lane; e < (16 * NT - 4 * NXQ) * (kBXRow / 8); e += 64)
     reinterpret_cast<uint4*>(s_xw + 4 * NXQ * kBXRow)[e] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  float4v acc_g[NT], acc_u[NT];
+  float4v acc_g[MA][NT], acc_u[MA][NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    acc_g[t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-    acc_u[t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-  }
+  for (int m = 0; m < MA; ++m)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      acc_g[m][t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+      acc_u[m][t] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+  // an FP16 tile, also a wide one, is one 16-row tile
   if (tier == 3)
-    bh_tier<3, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
+    bh_tier<3, 1, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
+  else if (tier == 2 && wide)
+    bh_tier<2, MA, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
   else if (tier == 2)
-    bh_tier<2, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
+    bh_tier<2, 1, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
+  else if (wide)
+    bh_tier<1, MA, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
   else
-    bh_tier<1, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
-  if (threadIdx.x < 16)
-    s_mask[threadIdx.x] = my_slot < n_slots && (int)threadIdx.x < nitems ? my_mask & (0xffffffffu >> (32 - B)) : 0u;
+    bh_tier<1, 1, NT, NXQ>(lane, w, d, G, B, x, rec, s_xw, s_sc, acc_g, acc_u);
+  if (threadIdx.x < 16) {
+#pragma unroll
+    for (int m = 0; m < MA; ++m)
+      s_mask[16 * m + threadIdx.x] = my_slot[m] < n_slots && 16 * m + (int)threadIdx.x < nitems
+                                         ? my_mask[m] & (0xffffffffu >> (32 - B))
+                                         : 0u;
+  }
   __syncthreads();  // every wave is done with its x rows: the partials take their bytes
   // partials of the waves -> LDS: [w][gate/up][row][col]
   float* s_part = reinterpret_cast<float*>(bh_lds);
   const int j = lane >> 4, col = lane & 15;
   constexpr int NC = 16 * NT;
+  constexpr int NR = 16 * MA;
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
+  for (int m = 0; m < MA; ++m)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s_part[((w * 2 + 0) * 16 + 4 * j + i) * NC + 16 * t + col] = acc_g[t][i];
-      s_part[((w * 2 + 1) * 16 + 4 * j + i) * NC + 16 * t + col] = acc_u[t][i];
-    }
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s_part[((w * 2 + 0) * NR + 16 * m + 4 * j + i) * NC + 16 * t + col] = acc_g[m][t][i];
+        s_part[((w * 2 + 1) * NR + 16 * m + 4 * j + i) * NC + 16 * t + col] = acc_u[m][t][i];
+      }
   __syncthreads();
   // h in the down kernel's layout: 4 items, batch row, next 4 items; zero past
   // the tile's items and the batch
-  const int per = tier == 3 ? 8 : 16;
+  const int per = (tier == 3 ? 8 : 16) << wide;
   const int local = item0 - (tier == 3 ? 0 : tier == 2 ? n3 : n3 + n2);
   float* hT = hB + (int64_t)(h_base(tier, n3, n2) + local) * NC;
   for (int e = threadIdx.x; e < per * NC; e += kBHThreads) {
     const int m = e & 3, b = (e >> 2) % NC, r = 4 * (e / (4 * NC)) + m;  // item, batch row
     float a = 0.0f, u = 0.0f;
     for (int q = 0; q < kBHWaves; ++q) {  // waves in a fixed order
-      a += s_part[((q * 2 + 0) * 16 + r) * NC + b];
-      u += s_part[((q * 2 + 1) * 16 + r) * NC + b];
+      a += s_part[((q * 2 + 0) * NR + r) * NC + b];
+      u += s_part[((q * 2 + 1) * NR + r) * NC + b];
     }
     // zero where row b did not select neuron r (or its slot is invalid); the
     // masks of padding items and the bits past the batch are zero
@@ -801,7 +862,10 @@ hipError_t launch_ffn_batch(m2c_layer* L, const uint16_t* x, int batch, const ui
     hipLaunchKernelGGL((ffn_bh_kernel<1, 4>), dim3(tiles), dim3(kBHThreads), 0, stream, x, d,
                        batch, counts, work_slot, work_mask, L->slots, sb, cap, n_slots, hB);
   } else {
-    hipLaunchKernelGGL((ffn_bh_kernel<2, 8>), dim3(tiles), dim3(kBHThreads), 0, stream, x, d,
+    // at most kBHWideTiles tiles, or wide ones
+    const int some = tiles < kBHWideTiles ? tiles : kBHWideTiles;
+    const int most = some > cap / 16 + 3 ? some : cap / 16 + 3;
+    hipLaunchKernelGGL((ffn_bh_kernel<2, 8>), dim3(most), dim3(kBHThreads), 0, stream, x, d,
                        batch, counts, work_slot, work_mask, L->slots, sb, cap, n_slots, hB);
   }
   hipError_t e = hipGetLastError();

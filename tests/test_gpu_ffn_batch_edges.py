@@ -1,6 +1,6 @@
 """Batched FFN where its tiles and steps end: tiers of 0, 1, 8, 16, 31, 32, 33
 ... items, quantization group counts that are no multiple of 16, one row tile
-and two, and rows of very different magnitude (the wave's exponent of the down
+and two, wide gate/up tiles, and rows of very different magnitude (the wave's exponent of the down
 kernel moves between steps), against the oracle. The tolerance is the suite's
 FFN tolerance (2e-3 of each value, floored at 1% of the row's rms)."""
 import numpy as np
@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d,batch,counts,xscale", [
     (128, 2, (0, 0, 1), 1.0), (256, 3, (1, 0, 0), 1.0), (384, 8, (8, 16, 31), 1.0),
     (640, 16, (9, 33, 32), 1.0), (1024, 17, (32, 31, 1), 1.0), (2048, 32, (17, 65, 130), 1.0),
-    (1152, 31, (0, 40, 0), 1.0), (512, 9, (70, 70, 300), 64.0), (4096, 5, (40, 200, 400), 2.0 ** -8)])
+    (1152, 31, (0, 40, 0), 1.0), (512, 9, (70, 70, 300), 64.0), (4096, 5, (40, 200, 400), 2.0 ** -8),
+    # above 16 rows, at most and more than 256 gate/up tiles of 16 items (8 of FP16)
+    (256, 17, (8, 16, 4064), 1.0), (256, 17, (8, 17, 4064), 1.0), (384, 32, (513, 1505, 1603), 1.0)])
 def test_batched_ffn_edges(d, batch, counts, xscale):
     from paper_2410_14740_amd import m2c
     from paper_2410_14740_amd import workloads as W
