@@ -264,16 +264,22 @@ __device__ __forceinline__ void bh_compute(const GroupA<TIER> (&A)[MT], const ui
 }
 
 // The loads of the next group, and the current one's x rows into LDS. With
-// wide tiles the next x rows are loaded only when the current ones have left
-// their registers (both sets do not fit).
+// wide tiles, and for 9 to 16 rows, the next x rows are loaded only when the
+// current ones have left their registers: both sets do not fit, or (9 to 16
+// rows) take 138 registers, one workgroup per CU, where one set takes 122 and
+// two fit. Both launches of a call (MI355X, before -> now): 16 rows 7B 39.9 ->
+// 36.4 us, 13B 43.1 -> 39.8, 70B 67.7 -> 65.2, d 1024 23.4 -> 20.7; where the
+// tiles are fewer than the CUs alike (d_ff 2752 at 12 rows 12.5, 12.7). At 8 rows
+// and below both sets fit twice.
 template <int TIER, int MT, int NXQ>
 __device__ __forceinline__ void bh_next(BhLoads<TIER, MT, NXQ>& next, BhLoads<TIER, MT, NXQ>& cur,
                                         const uint16_t* x, const uint8_t* const* rec, int d, int B,
                                         int grp, uint16_t* s_xw, int lane) {
-  if (MT == 1) next.issue_x(x, d, B, grp, lane);
+  constexpr bool late = MT > 1 || NXQ == 4;
+  if (!late) next.issue_x(x, d, B, grp, lane);
   next.issue_a(rec, d, grp, lane);
   cur.stage(s_xw, B, lane);
-  if (MT > 1) {
+  if (late) {
     __builtin_amdgcn_sched_barrier(0);
     next.issue_x(x, d, B, grp, lane);
   }
