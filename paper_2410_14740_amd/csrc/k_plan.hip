@@ -12,9 +12,9 @@
 //   plan_place_kernel  every output, at its final place. Ranks in id order
 //       are the counts of the chunks before plus wave ballots. The victims of
 //       the NEW neurons are the unstamped slots in LRU order: every workgroup
-//       ranks the whole order for itself (a few coalesced loads and ballots
-//       per thread, cheaper than a launch to share it) and keeps those its
-//       own NEW neurons take. The workgroups past the neuron chunks write the
+//       ranks the order for itself (a few coalesced loads and ballots per
+//       thread, cheaper than a launch to share it; of a long order only what
+//       it needs) and keeps those its own NEW neurons take. The workgroups past the neuron chunks write the
 //       new LRU order: the unstamped slots beyond the victims in their old
 //       order, then every slot used this step in slot order (they share the
 //       largest last use), which keeps it sorted by (last use, slot).
@@ -23,7 +23,10 @@
 // lie back to back (FP16, INT8, INT4), and ranks count from each pool's start.
 //
 // What bounds it: latency -- two launches, two dependent memory round trips
-// in each, and block-wide ranks -- not bytes (about 13 d_ff + 30 C + 60 |R|).
+// in each, and block-wide ranks -- not bytes: about 13 d_ff + 30 C + 60 |R| from
+// HBM, and from L2 12 C more of the LRU order for each of the d_ff / 256 + C / 1024
+// workgroups (10 MB at d_ff 28672 with 7000 slots). Of more than 8192 slots that
+// read is a sweep at a time, and grows with d_ff C: see plan_long.
 // One workgroup doing the whole step was bound by one CU's instruction issue
 // and a dozen dependent round trips, and the pools took two launches more.
 // Measured (MI355X, rocprofv3 kernel time, all plan launches and the FFN's
@@ -186,8 +189,9 @@ __global__ __launch_bounds__(kPC) void plan_classify_kernel(const uint8_t* __res
 }
 
 // Ranks of the set flags among kPRounds per thread, entry order (round, wave,
-// lane): *before the caller's entry r of the set ones is rank[r] (rounds past
-// `rounds` are not touched). cnt: kPRounds * kPW words, written here before
+// lane): rank[r] is base plus the set ones before the caller's entry r (every
+// rank[r] is written; flags of rounds past `rounds` count as not set), and base
+// ends as base plus all of them. cnt: kPRounds * kPW words, written here before
 // the caller's barrier (store) and read after it (read).
 struct BlockRanks {
   unsigned long long bal[kPRounds];
@@ -226,7 +230,9 @@ struct PlaceArgs {
   TaskTable tt;
 };
 
-template <bool POOLS>
+// LONG: an order of several sweeps, of which a workgroup ranks only the part it
+// needs (plan_long says when).
+template <bool POOLS, bool LONG>
 __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
   constexpr int NP = POOLS ? 3 : 1;
   __shared__ uint32_t s_tot[kPW], s_pre[kPW], s_own[kPW];  // fields: all chunks, those before, this one
@@ -253,9 +259,21 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
   const uint32_t mask = a.one_row || !neurons ? 1u : st.masks[min(n, a.d_ff - 1)];
   const int serial = st.plan_copy[kPlanSerial], cur = st.plan_copy[kPlanCur];
   const int rounds_all = (g.total + kPT - 1) / kPT;
+  // LONG: the pools whose order the workgroup ranks, and the round its first
+  // sweep starts at. One that writes the new order ranks the pools of its own
+  // places; a neuron workgroup learns below which ones its NEW neurons go to.
+  bool need[3] = {!neurons, false, false};
+  int r_first = 0;
+  if (LONG && POOLS && !neurons) {
+#pragma unroll
+    for (int q = NP - 1; q >= 0; --q) {
+      need[q] = g.C[q] > 0 && g.rf[q] < (own_round + 1) * kPT && g.rf[q] + g.C[q] > own_round * kPT;
+      if (need[q]) r_first = g.rf[q] / kPT;
+    }
+  }
   int32_t* lru_out = st.lru + (int64_t)(1 - cur) * g.total;
   int32_t* pos_out = st.lru_pos + (int64_t)(1 - cur) * g.total;
-  // both orders are read, so that the loads do not wait for `cur`
+  // the first sweep reads both orders, so that its loads do not wait for `cur`
   int tp[kPRounds], sv[kPRounds], sw[kPRounds];
   auto load_lru = [&](int r0) {
 #pragma unroll
@@ -269,7 +287,7 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
       }
     }
   };
-  load_lru(0);
+  load_lru(r_first);
   if (wave < kPFields) {
     uint32_t tot = 0, pre = 0, own = 0;
     for (int c0 = 0; c0 < a.chunks; c0 += 64) {
@@ -303,10 +321,18 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
     for (int f = 0; f < 7; ++f) reinterpret_cast<uint32_t*>(&s_cw[f])[wave] = c[f];
   }
 
-  // ---- the LRU order: rank every unstamped place, hand out victims
+  // ---- the LRU order: rank the unstamped places, hand out victims. LONG: a
+  // neuron workgroup ranks, in the pools its NEW neurons go to, the places up to
+  // its last victim; one that writes the new order those of its pools up to its
+  // own places and up to the first place kept.
   uint32_t base = 0;
-  int r0 = 0;
+  int r0 = r_first;
   uint32_t nnew[3] = {0, 0, 0}, npre[3] = {0, 0, 0}, nown[3] = {0, 0, 0};
+  // unstamped places of a pool: of its required neurons, all but the NEW ones stamped a slot
+  auto unstamped = [&](int q, uint32_t n_new) {
+    return (uint32_t)g.C[q] - (POOLS ? s_tot[kR3 + q] : s_tot[kR3] + s_tot[kR2] + s_tot[kR1]) + n_new;
+  };
+  uint32_t want[3] = {0, 0, 0};  // unstamped places of the pool that have to be ranked
   do {
     bool unt[kPRounds];
     const int rounds = min(rounds_all - r0, kPRounds);
@@ -316,13 +342,18 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
     BlockRanks br;
     br.store(unt, rounds, s_cnt, wave, lane);
     __syncthreads();
-    if (r0 == 0) {
+    if (r0 == r_first) {
       if (s_tot[kR3] + s_tot[kR2] + s_tot[kR1] > (uint32_t)a.cap) break;  // workgroup-uniform
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
         nnew[q] = s_tot[POOLS ? kF3 + q : kNew];
         npre[q] = s_pre[POOLS ? kF3 + q : kNew];
         nown[q] = s_own[POOLS ? kF3 + q : kNew];
+        if (LONG) {
+          const uint32_t n_unt = unstamped(q, nnew[q]);
+          if (neurons) need[q] = nown[q] > 0 && npre[q] < n_unt;
+          want[q] = min(neurons ? npre[q] + nown[q] : nnew[q] + 1u, n_unt);
+        }
       }
     }
     uint32_t rank[kPRounds];
@@ -335,11 +366,11 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
           const int q = pool_of(p);
           const int q0 = pick(q, g.rf[0], g.rf[1], g.rf[2]), qc = pick(q, g.C[0], g.C[1], g.C[2]);
           if (p == q0) s_lo[q] = rank[r];
-          if (p == q0 + qc - 1) s_hi[q] = rank[r] + unt[r];
+          if (!LONG && p == q0 + qc - 1) s_hi[q] = rank[r] + unt[r];
         }
       }
       __syncthreads();
-    } else if (tid == 0) {
+    } else if (!LONG && tid == 0) {
       s_hi[0] = base;
     }
 #pragma unroll
@@ -362,8 +393,28 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
         }
       }
     }
-    r0 += kPRounds;
-    if (r0 < rounds_all) load_lru(r0);
+    if constexpr (LONG) {
+      // the next sweep: behind this one, at the start of the next pool to rank, or none
+      const int end = r0 + kPRounds;
+      r0 = rounds_all;
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+        if (need[q] && g.rf[q] + g.C[q] > end * kPT &&
+            (g.rf[q] >= end * kPT || base - (POOLS ? s_lo[q] : 0u) < want[q] || own_round >= end))
+          r0 = min(r0, max(end, g.rf[q] / kPT));
+#pragma unroll
+      for (int r = 0; r < kPRounds; ++r) {
+        tp[r] = sv[r] = sw[r] = 0;
+        if (r0 + r < rounds_all) {
+          const int p = min((r0 + r) * kPT + tid, g.total - 1);
+          tp[r] = st.touch_pos[p];
+          sv[r] = sw[r] = st.lru[(int64_t)cur * g.total + p];
+        }
+      }
+    } else {
+      r0 += kPRounds;
+      if (r0 < rounds_all) load_lru(r0);
+    }
     __syncthreads();
   } while (r0 < rounds_all);
 
@@ -388,7 +439,7 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     filled[q] = st.plan_copy[kPlanFilled + q];
-    nunt[q] = (int)(s_hi[q] - s_lo[q]);
+    nunt[q] = LONG ? (int)unstamped(q, nnew[q]) : (int)(s_hi[q] - s_lo[q]);
     nv[q] = min((int)nnew[q], nunt[q]);
     ne[q] = min(nv[q], g.C[q] - filled[q]);  // never-used slots come first in the order
   }
@@ -398,7 +449,7 @@ __global__ __launch_bounds__(kPT) void plan_place_kernel(const PlaceArgs a) {
     // to the end of their pool's order, in slot order
     const int32_t* pos_in = st.lru_pos + (int64_t)cur * g.total;
     base = 0;
-    for (r0 = 0; r0 <= own_round; r0 += kPRounds) {
+    for (r0 = r_first; r0 <= own_round; r0 += kPRounds) {
       const int rounds = min(own_round + 1 - r0, kPRounds);
       int ts[kPRounds], ps[kPRounds];
 #pragma unroll
@@ -599,6 +650,20 @@ static PlanPtrs plan_ptrs(const m2c_layer* L, uint8_t* plan) {
   return P;
 }
 
+// Whether the place kernel ranks only the parts of the LRU order it needs. Asking
+// which costs scalar registers: about 1 us of a plan with pools, 0.1 to 0.5 with one
+// order. With one sweep (8192 slots) there is nothing to leave out. With pools the
+// workgroups of the later ones skip the earlier pools' sweeps; a single order's last
+// workgroup ranks nearly all of it, and only the reads of the others are saved.
+// Measured (MI355X, whole plans back to back, all of the order -> the parts):
+//   pools, d_ff 28672: 2867 slots 12.3 -> 13.4 us; d_ff 32768: 8192 slots 14.8 ->
+//   14.6, 16384 23.2 -> 21.1, 32768 39.6 -> 30.1
+//   single: 9000 slots 14.2 -> 14.7, 28672 25.3 -> 25.6, 41000 35.8 -> 35.1, 65536
+//   71 -> 52, 262144 535 -> 199
+static bool plan_long(bool pools, int slots) {
+  return slots > (pools ? kPRounds * kPT : 5 * kPRounds * kPT);
+}
+
 hipError_t launch_plan(m2c_layer* L, const uint8_t* tier_map, int batch, int step, uint8_t* plan,
                        hipStream_t stream) {
   const int d_ff = L->desc.d_ff;
@@ -635,10 +700,15 @@ hipError_t launch_plan(m2c_layer* L, const uint8_t* tier_map, int batch, int ste
 #undef M2C_CLASSIFY
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (L->pools)
-    hipLaunchKernelGGL(plan_place_kernel<true>, gp, b, 0, stream, a);
+  const bool many = plan_long(L->pools, a.g.total);
+  if (L->pools && many)
+    hipLaunchKernelGGL((plan_place_kernel<true, true>), gp, b, 0, stream, a);
+  else if (L->pools)
+    hipLaunchKernelGGL((plan_place_kernel<true, false>), gp, b, 0, stream, a);
+  else if (many)
+    hipLaunchKernelGGL((plan_place_kernel<false, true>), gp, b, 0, stream, a);
   else
-    hipLaunchKernelGGL(plan_place_kernel<false>, gp, b, 0, stream, a);
+    hipLaunchKernelGGL((plan_place_kernel<false, false>), gp, b, 0, stream, a);
   return hipGetLastError();
 }
 

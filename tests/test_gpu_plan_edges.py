@@ -1,5 +1,6 @@
 """Cache plans at the edges of the plan kernels' tiling, against the oracle on
-given tier maps: chunks of 1024 neurons, sweeps of 8192 LRU entries, pools
+given tier maps: chunks of 256 neurons, rounds of 1024 and sweeps of 8192 LRU
+places, orders of many sweeps, of which a workgroup ranks only a part, pools
 that start and end inside them, empty pools, and a captured plan replayed
 with changing tier maps."""
 import numpy as np
@@ -57,7 +58,13 @@ def _check(L, o, label):
 @pytest.mark.parametrize("d_ff,k,C,batch,dom", [
     (1, 1, 1, 1, 0), (1023, 300, 500, 1, 1), (1024, 300, 0, 1, 0), (1025, 400, 1024, 2, 0),
     (9000, 1500, 8192, 1, 0), (9000, 1500, 8193, 3, 1), (20000, 2500, 17000, 1, 1),
-    (66000, 3000, 4097, 1, 0)])
+    (66000, 3000, 4097, 1, 0),
+    # chunks of 256 neurons and rounds of 1024 places
+    (255, 100, 200, 1, 0), (256, 256, 100, 2, 1), (257, 120, 257, 1, 0), (2049, 500, 1025, 5, 0),
+    (5000, 800, 2048, 1, 1),
+    # orders of several sweeps: bypass beyond them, nearly all new, 13 sweeps, every slot of the largest layer
+    (30000, 12000, 9000, 1, 0), (60000, 15000, 40961, 1, 0), (33000, 16000, 16385, 2, 1), (100000, 3000, 100000, 1, 1),
+    (262144, 1000, 262144, 2, 0)])
 def test_plan_single_arena_edges(d_ff, k, C, batch, dom):
     from paper_2410_14740_amd import m2c
     L = _layer(d_ff, k, C, batch, m2c.FLAG_DOMINANT_HITS if dom else 0)
@@ -81,7 +88,11 @@ def test_plan_single_arena_edges(d_ff, k, C, batch, dom):
 @pytest.mark.parametrize("d_ff,k,slots", [
     (1024, 200, {3: 1, 2: 1, 1: 1}), (3000, 700, {3: 1024, 2: 1000, 1: 24}),
     (3000, 700, {3: 0, 2: 0, 1: 300}), (3000, 700, {3: 300, 2: 0, 1: 0}),
-    (32768, 4000, {3: 8191, 2: 2, 1: 9000}), (32768, 4000, {3: 800, 2: 8192, 1: 8193})])
+    (32768, 4000, {3: 8191, 2: 2, 1: 9000}), (32768, 4000, {3: 800, 2: 8192, 1: 8193}),
+    # orders of several sweeps: pools of several each, one inside a sweep, empty ones, one full at the start
+    (32768, 3000, {3: 10000, 2: 9000, 1: 13768}), (32768, 9000, {3: 300, 2: 24000, 1: 8468}),
+    (32768, 5000, {3: 0, 2: 9000, 1: 20000}), (32768, 12000, {3: 9000, 2: 0, 1: 9001}),
+    (20000, 6000, {3: 500, 2: 16384, 1: 100})])
 def test_plan_pool_edges(d_ff, k, slots, dom):
     from paper_2410_14740_amd import m2c
     L = _layer(d_ff, k, 0, 1, m2c.FLAG_DOMINANT_HITS if dom else 0, slots)
