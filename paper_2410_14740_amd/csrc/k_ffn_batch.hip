@@ -456,7 +456,7 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
 // magnitudes.
 //
 // A group's items are cut into steps of 32 of one tier (FP16, INT8, INT4); each
-// wave of the group's workgroups takes an equal run of them, so that most
+// wave of the group's workgroups takes a run of them, so that most
 // waves see one tier (steps dealt in turn, a share of every tier per wave,
 // cost a load round trip per tier: 13.2 instead of 12.1 us at batch 8). In a
 // step lane (x, j) (x = lane % 16, j = lane / 16) loads the 8
@@ -765,10 +765,20 @@ __global__ __launch_bounds__(kDMThreads, 2) void ffn_bdn_kernel(
   const int S3 = (n3 + kDMStep - 1) / kDMStep, S2 = (n2 + kDMStep - 1) / kDMStep;
   const int S1 = (n1 + kDMStep - 1) / kDMStep;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wg = blockIdx.x / G, W = (gridDim.x / G) * kDMWaves, ST = S3 + S2 + S1;
-  if ((int64_t)ST * wg * kDMWaves / W == (int64_t)ST * (wg + 1) * kDMWaves / W) return;  // no steps
-  const int gw = wg * kDMWaves + w;
-  const int lo = (int)((int64_t)ST * gw / W), hi = (int)((int64_t)ST * (gw + 1) / W);
+  // All the group's waves share its steps equally, or, where that is at most two
+  // steps each, as few of them as have one (two) each: the workgroups left over
+  // have none, and no atomics. Both launches of a call (MI355X, shared equally ->
+  // this): d 2048 of d_ff 5632 at 2 / 32 rows 13.2 / 27.6 -> 12.5 / 25.3 us, d 1024
+  // of 11008 at 32 rows 32.2 -> 30.1, d 4096 of 4000 28.4 -> 27.1. Longer equal runs
+  // on fewer waves leave SIMDs idle (d 2048, 24 rows, 2.06 steps each or 3 on 88 of
+  // 128 waves: 35.8, 36.7; the 70B shape at 32 rows, 14.4 or 15: 102.3, 104.9).
+  const int wg = blockIdx.x / G, ST = S3 + S2 + S1;
+  int W = (gridDim.x / G) * kDMWaves;
+  if (ST <= 2 * W) W = ST <= W ? ST : (ST + 1) / 2;
+  if (wg * kDMWaves >= W) return;  // no steps (workgroup-uniform)
+  const int gw = min(wg * kDMWaves + w, W);  // W: no steps
+  const int lo = (int)((uint32_t)(ST * gw) / (uint32_t)W);
+  const int hi = (int)((uint32_t)(ST * min(gw + 1, W)) / (uint32_t)W);
   const int lane = threadIdx.x & 63, x = lane & 15, j = lane >> 4;
   // the wave's run of the group's steps, by tier
   const int st3 = lo, st2 = max(lo - S3, 0), st1 = max(lo - S3 - S2, 0);
