@@ -77,9 +77,16 @@ __device__ __forceinline__ half4v i8x4_to_h4(uint32_t w) {
 }
 
 // The h values, written by the gate/up kernel and read by the down kernel as
-// matrix-core operands: 4 consecutive items of one tier, then the batch row
-// (Bp = 16 or 32 rows, zeros past the batch), then the next 4 items, each
-// tier's items from a multiple of 32 (h_base + the item's place in its tier).
+// matrix-core operands: 4 consecutive items of one tier, then the batch row,
+// then the next 4 items, each tier's items from a multiple of 32 (h_base + the
+// item's place in its tier). Up to 16 rows only the batch's are stored: every
+// workgroup of the down kernel reads these bytes, and at 2 rows padding to 16
+// makes them eight times as many. Above, there are 32, zeros past the batch (a
+// stride that is no constant cost 1 to 2% at 32 rows).
+template <int NT>
+__device__ __forceinline__ int h_rows(int B) {
+  return NT == 1 ? B : 16 * NT;
+}
 constexpr int kHAlign = 32;
 __device__ __forceinline__ int h_base(int tier, int n3, int n2) {
   const int p3 = (n3 + kHAlign - 1) / kHAlign * kHAlign;
@@ -431,9 +438,10 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
   // the tile's items and the batch
   const int per = (tier == 3 ? 8 : 16) << wide;
   const int local = item0 - (tier == 3 ? 0 : tier == 2 ? n3 : n3 + n2);
-  float* hT = hB + (int64_t)(h_base(tier, n3, n2) + local) * NC;
+  float* hT = hB + (int64_t)(h_base(tier, n3, n2) + local) * h_rows<NT>(B);
   for (int e = threadIdx.x; e < per * NC; e += kBHThreads) {
-    const int m = e & 3, b = (e >> 2) % NC, r = 4 * (e / (4 * NC)) + m;  // item, batch row
+    const int m = e & 3, b = (e >> 2) % NC, q4 = e / (4 * NC), r = 4 * q4 + m;  // item, batch row
+    if (b >= h_rows<NT>(B)) continue;
     float a = 0.0f, u = 0.0f;
     for (int q = 0; q < kBHWaves; ++q) {  // waves in a fixed order
       a += s_part[((q * 2 + 0) * NR + r) * NC + b];
@@ -441,7 +449,7 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
     }
     // zero where row b did not select neuron r (or its slot is invalid); the
     // masks of padding items and the bits past the batch are zero
-    hT[e] = (s_mask[r] >> b) & 1u ? silu_mul(a, u) : 0.0f;
+    hT[(q4 * h_rows<NT>(B) + b) * 4 + m] = (s_mask[r] >> b) & 1u ? silu_mul(a, u) : 0.0f;
   }
 }
 
@@ -562,7 +570,8 @@ __device__ __forceinline__ uint32_t dm_offset(uint32_t v) { return v ^ 0x8888888
 
 // The loads of one step; the slot ids come first (their own struct, one step
 // further ahead). Every load is unconditional: items past the tier's last
-// read the zero slot and whatever h words follow, and are masked.
+// read the zero slot and whatever h words follow, and are masked; rows past
+// the batch that are not stored repeat its last one (their sums are dropped).
 typedef int int4u __attribute__((ext_vector_type(4), aligned(4)));
 struct DmSlots {
   int4u s[2];
@@ -579,7 +588,7 @@ struct DmLoads {
   half2v sc[2][2];  // two fp16 scales per register
   float4v h[2][NT];
   __device__ __forceinline__ void issue(const DmSlots& sl, int i0, int n, const float* __restrict__ hT,
-                                        const uint8_t* __restrict__ slots, int64_t slot_bytes,
+                                        int B, const uint8_t* __restrict__ slots, int64_t slot_bytes,
                                         int n_slots, int64_t doff, int64_t soff, int x, int j) {
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -596,7 +605,8 @@ struct DmLoads {
 #pragma unroll
       for (int t = 0; t < NT; ++t)
         h[a][t] = *reinterpret_cast<const float4v*>(
-            hT + ((int64_t)((i0 + 16 * a) / 4 + j) * (16 * NT) + 16 * t + x) * 4);
+            hT + ((int64_t)((i0 + 16 * a) / 4 + j) * h_rows<NT>(B) +
+                  (NT == 1 ? min(x, B - 1) : 16 * t + x)) * 4);
   }
 };
 
@@ -707,7 +717,7 @@ __device__ __forceinline__ void dm_step(const DmLoads<TIER, NT>& L, int i0, int 
 template <int TIER, int NT>
 __device__ __forceinline__ void dm_tier(DmSlots sl, int first, int end, int n,
                                         const int32_t* __restrict__ ids,
-                                        const float* __restrict__ hT, int grp, int d, int G,
+                                        const float* __restrict__ hT, int B, int grp, int d, int G,
                                         const uint8_t* __restrict__ slots, int64_t slot_bytes,
                                         int n_slots, int (&E)[NT], float4v (&acc)[2][8]) {
   if (first >= end) return;  // wave-uniform
@@ -720,7 +730,7 @@ __device__ __forceinline__ void dm_tier(DmSlots sl, int first, int end, int n,
   auto at = [&](int st) { return kDMStep * (st < end ? st : first); };
   DmLoads<TIER, NT> L0, L1;
   auto load = [&](DmLoads<TIER, NT>& L, int i0) {
-    L.issue(sl, i0, n, hT, slots, slot_bytes, n_slots, doff, soff, x, j);
+    L.issue(sl, i0, n, hT, B, slots, slot_bytes, n_slots, doff, soff, x, j);
   };
   load(L0, at(first));
   sl.issue(ids, at(first + 1), j);
@@ -796,11 +806,11 @@ __global__ __launch_bounds__(kDMThreads, 2) void ffn_bdn_kernel(
   int E[NT];  // above every exponent until a row's first value sets it
 #pragma unroll
   for (int t = 0; t < NT; ++t) E[t] = 1 << 10;
-  constexpr int Bp = 16 * NT;
-  dm_tier<3, NT>(sl3, st3, en3, n3, work_slot, hB, grp, d, G, slots, slot_bytes, n_slots, E, acc);
-  dm_tier<2, NT>(sl2, st2, en2, n2, ids2, hB + (int64_t)h_base(2, n3, n2) * Bp, grp, d, G, slots,
+  dm_tier<3, NT>(sl3, st3, en3, n3, work_slot, hB, B, grp, d, G, slots, slot_bytes, n_slots, E, acc);
+  const int64_t rows = h_rows<NT>(B);
+  dm_tier<2, NT>(sl2, st2, en2, n2, ids2, hB + h_base(2, n3, n2) * rows, B, grp, d, G, slots,
                  slot_bytes, n_slots, E, acc);
-  dm_tier<1, NT>(sl1, st1, en1, n1, ids1, hB + (int64_t)h_base(1, n3, n2) * Bp, grp, d, G, slots,
+  dm_tier<1, NT>(sl1, st1, en1, n1, ids1, hB + h_base(1, n3, n2) * rows, B, grp, d, G, slots,
                  slot_bytes, n_slots, E, acc);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
