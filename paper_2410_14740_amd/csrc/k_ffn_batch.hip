@@ -847,17 +847,23 @@ __global__ __launch_bounds__(kDMThreads, 2) void ffn_bdn_kernel(
   }
 }
 
-// One round of workgroups, two per CU (the registers' limit), and so one set
-// of atomics per two waves of a SIMD: 512 in all, or fewer where the plan's
-// capacity has no step for them. With 512-thread workgroups 256 / 512 / 1024
-// took 13.5 / 16.1 / 19.3 us (7B, batch 8) and 41.7 / 51.1 / 63.6 (70B, 32).
+// One round of workgroups, two per CU (the registers' limit), and so one set of
+// atomics per two waves of a SIMD: 512 on the 256 CUs, or fewer where the plan's
+// capacity has no step for them. 256 / 512 / 1024 workgroups, both launches of a
+// call (MI355X): 7B at 8 rows 26.9 / 26.3 / 30.7 us, 70B shape at 32 rows 107.1 /
+// 104.4 / 109.6. With at most 8 groups 512 are 64 or more that add into the same
+// columns, and 256 are faster: d 1024 of d_ff 30000 at 8 / 32 rows 23.3 / 46.5 ->
+// 22.9 / 42.7 us, d 256 of 60000 at 8 rows 34.1 -> 30.9 (at 12 groups, d 1536 of
+// 20000 at 4 rows, fewer are slower: 21.3 -> 22.0).
 constexpr int kDMGrid = 512;
+constexpr int kDMFewGroups = 8;
 static void launch_bdn(int d, int batch, int cap, hipStream_t stream, const int32_t* counts,
                        const int32_t* work_slot, const float* hB, const uint8_t* slots,
                        int64_t sb, int n_slots, float* y) {
   const int G = d >> 7;
   const int most = (cap / kDMStep + 3 + kDMWaves - 1) / kDMWaves;
-  int per = kDMGrid > G ? kDMGrid / G : 1;
+  const int grid = G <= kDMFewGroups ? kDMGrid / 2 : kDMGrid;
+  int per = grid > G ? grid / G : 1;
   if (per > most) per = most;
   if (batch <= 16)
     hipLaunchKernelGGL(ffn_bdn_kernel<1>, dim3(G * per), dim3(kDMThreads), 0, stream, d, batch,
