@@ -360,19 +360,30 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
   // branch-free masks.
   int u[16 * MA];
 #pragma unroll
-  for (int k = 0; k < 16 * MA; ++k) {
-    const int s = __builtin_amdgcn_readfirstlane(work_slot[item0 + k]);
-    u[k] = k < nitems && s >= 0 && s < n_slots ? s : n_slots;  // zero slot for padding
+  for (int m = 0; m < MA; ++m) {
+#pragma unroll
+    for (int k = 16 * m; k < 16 * m + 16; ++k) u[k] = n_slots;  // zero slot for padding
+    if (m == 0 || wide) {  // workgroup-uniform: tiles of 16 skip the second half's work
+#pragma unroll
+      for (int k = 16 * m; k < 16 * m + 16; ++k) {
+        const int s = __builtin_amdgcn_readfirstlane(work_slot[item0 + k]);
+        u[k] = k < nitems && s >= 0 && s < n_slots ? s : n_slots;
+      }
+    }
   }
   int my_slot[MA];
   uint32_t my_mask[MA];  // stored after the main loop
   const uint8_t* rec[MA];
 #pragma unroll
   for (int m = 0; m < MA; ++m) {
-    my_slot[m] = 0;
+    my_slot[m] = n_slots;
+    my_mask[m] = 0;
+    if (m == 0 || wide) {
+      my_slot[m] = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) my_slot[m] |= u[16 * m + k] & -((lane & 15) == k);
-    my_mask[m] = work_mask[min(item0 + 16 * m + (lane & 15), cap - 1)];
+      for (int k = 0; k < 16; ++k) my_slot[m] |= u[16 * m + k] & -((lane & 15) == k);
+      my_mask[m] = work_mask[min(item0 + 16 * m + (lane & 15), cap - 1)];
+    }
     rec[m] = slots + (int64_t)my_slot[m] * slot_bytes;
   }
   // the tile's gate and up scales (4 G contiguous bytes per record) into LDS
@@ -426,13 +437,15 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
   constexpr int NR = 16 * MA;
 #pragma unroll
   for (int m = 0; m < MA; ++m)
+    if (m == 0 || wide) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+      for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        s_part[((w * 2 + 0) * NR + 16 * m + 4 * j + i) * NC + 16 * t + col] = acc_g[m][t][i];
-        s_part[((w * 2 + 1) * NR + 16 * m + 4 * j + i) * NC + 16 * t + col] = acc_u[m][t][i];
-      }
+        for (int i = 0; i < 4; ++i) {
+          s_part[((w * 2 + 0) * NR + 16 * m + 4 * j + i) * NC + 16 * t + col] = acc_g[m][t][i];
+          s_part[((w * 2 + 1) * NR + 16 * m + 4 * j + i) * NC + 16 * t + col] = acc_u[m][t][i];
+        }
+    }
   __syncthreads();
   // h in the down kernel's layout: 4 items, batch row, next 4 items; zero past
   // the tile's items and the batch
