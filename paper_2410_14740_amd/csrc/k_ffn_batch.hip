@@ -126,10 +126,12 @@ __device__ __forceinline__ void bh_tile(int b, int n3, int n2, int n1, int wide,
 // Above 16 rows a workgroup holds a CU alone (its registers), and each reads
 // all of x (32 rows: as many bytes as 2 to 4 tiles' INT8 or INT4 codes). Wide
 // tiles halve those reads and the rounds of workgroups; they are taken when the
-// tiles of 16 are more than one per CU. Measured (MI355X, both launches of a call,
-// tiles of 16 -> wide): 70B shape at 32 rows (935 tiles of 16) 121.5 -> 105.2 us,
-// 13B (640) 63.1 -> 61.5, d 4096 (341) 38.0 -> 35.8, d 12288 (269) 67.9 -> 63.5;
-// even where the wide ones just miss one round (7B at 17 rows, 529: 46.0, 46.7).
+// tiles of 16 are more than one per CU (256 CUs). Measured (MI355X, both launches
+// of a call, tiles of 16 -> wide): 70B shape at 32 rows (935 tiles of 16) 121.5 ->
+// 105.2 us, 13B (640) 67.3 -> 64.6, d 12288 (269) 68.7 -> 64.3, d 1024 (2000) 58.0 ->
+// 47.0; with 260 to 1200 tiles and d 256 to 8192, at 17 and 32 rows, all between 0
+// and 17% faster but one (d 8192 at 17 rows with 600, where the wide ones just miss
+// one round: 82.1, 83.1).
 constexpr int kBHWideTiles = 256;
 
 // One group (128 columns) of a tile on the matrix cores, as four
@@ -492,15 +494,21 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
 // workgroup per run of 128 .. 512 items, as before, spent most of its time on
 // atomics (B x 128 per run and group; 12 M of them at 32 rows of the 70B
 // shape) and on empty workgroups of a grid sized for the plan's capacity.
-// Measured (MI355X, rocprofv3 kernel time, before -> now): 70B
-// shape at 32 rows 104 -> 43.7 us, 7B at 8 rows 13.1 -> 12.6.
+// Measured (MI355X, rocprofv3 kernel time, before -> now): 70B shape at 32 rows
+// 105 -> 41.9 us, 7B at 8 / 17 / 32 rows 11.8 / 28.9 / 36.0 -> 10.7 / 17.0 / 20.8.
+// What it costs: its registers leave two waves per SIMD, and a run's second step
+// waits for a memory round trip of its own, where the runs before had five waves
+// and all of a run in flight. With 2 to 8 rows and two or more steps per wave that
+// shows: a call at d 1536 of d_ff 20000 with 4 rows 20.2 -> 21.2 us, d 1024 of
+// 30000 18.9 -> 19.8, d 2048 of 11008 17.4 -> 18.1. Three waves per SIMD (168
+// registers) spill 222 values: 7B at 8 rows 25.8 -> 46.8 us a call.
 
 constexpr int kDMThreads = 256;
 constexpr int kDMWaves = kDMThreads / 64;
 constexpr int kDMRegions = kDMWaves / 2;  // LDS partial results per workgroup
 constexpr int kDMStep = 32;               // items per step
 // a wave reads the slot ids of whole steps, two steps ahead
-static_assert(kDMStep <= kWorkSlotPad, "steps longer than the plan's spare work_slot entries");
+static_assert(2 * kDMStep <= kWorkSlotPad, "steps longer than the plan's spare work_slot entries");
 static_assert(kDMStep == kHAlign, "a step's h starts at a multiple of its length");
 
 // The 8 codes of one neuron at the lane's columns: 16 bytes of FP16, 8 of
@@ -769,9 +777,9 @@ __global__ __launch_bounds__(kDMThreads, 2) void ffn_bdn_kernel(
     const float* __restrict__ hB, const uint8_t* __restrict__ slots, int64_t slot_bytes, int cap,
     int n_slots, float* __restrict__ y) {
   constexpr int kRow = 132;  // 128 columns (in the order 16 e + x) and a pad against bank conflicts
-  // [region][batch row][column]: waves 0..3 store their partial rows, then
-  // waves 4..7 add theirs to them, so that every LDS word has one writer at a
-  // time (LDS float atomics are slow)
+  // [region][batch row][column]: the first half of the waves store their partial
+  // rows, then the others add theirs to them, so that every LDS word has one
+  // writer at a time (LDS float atomics are slow)
   __shared__ float s_y[kDMRegions][16 * NT][kRow];
   const int G = d >> 7;
   int grp = blockIdx.x % G;
