@@ -61,6 +61,14 @@ struct TreeOut {
   }
 };
 
+// Chunks of a row whose x is in flight together: the most that divide its NCH
+// with at most 16 loads for the NB tokens.
+constexpr int x_chunks(int nch, int nb) {
+  int q = nch;
+  while (q > 1 && (q * nb > 16 || nch % q)) --q;
+  return q;
+}
+
 // z[b][j], tokens NB blockIdx.y .. of the batch (the last group re-reads the
 // last token). A lane's partial takes chunks sl, sl + L, ... of its row: all
 // of them are loaded before the first fmaf (NCH >= chunks / L per lane).
@@ -82,7 +90,8 @@ __global__ __launch_bounds__(kPredThreads) void pred_z_kernel(const uint16_t* __
   float acc[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) acc[b] = 0.0f;
-  constexpr int QB = NCH * NB <= 16 ? NCH : 16 / NB;  // chunks whose x is in flight together
+  constexpr int QB = x_chunks(NCH, NB);
+  static_assert(NCH % QB == 0, "a pass has no chunks past the row's");
 #pragma unroll
   for (int q0 = 0; q0 < NCH; q0 += QB) {
     uint4 xv[QB][NB];

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d,r,d_ff,batch", [
     (128, 8, 1, 1), (128, 16, 70, 3), (256, 24, 333, 2), (384, 48, 65, 5), (512, 64, 257, 9),
     (640, 136, 1000, 1), (1024, 256, 513, 8), (1536, 400, 300, 17), (2176, 512, 129, 4),
-    (5120, 1024, 200, 1), (6144, 520, 90, 2), (8192, 512, 1030, 32), (16384, 1000, 100, 3)])
+    (5120, 1024, 200, 1), (5120, 256, 300, 2), (4224, 64, 100, 2), (6144, 520, 90, 2), (8192, 512, 1030, 32), (16384, 1000, 100, 3)])
 def test_scores_at_tile_edges(d, r, d_ff, batch):
     from paper_2410_14740_amd import m2c
     from paper_2410_14740_amd import workloads as W
