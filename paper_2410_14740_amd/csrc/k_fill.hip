@@ -6,7 +6,9 @@
 // copy is a device gather kernel that reads host memory over the host link:
 // no device-to-host round trip is needed to learn what to copy, and the
 // whole step stays on the GPU's queues. One workgroup copies one record at a
-// time with 16-byte loads, four in flight per thread.
+// time with 16-byte loads: four in flight per thread over the part of a record
+// that fills 16 KB blocks, one in flight over the rest (INT4 up to d 8192 and INT8
+// up to d 4096 are mostly or all rest).
 //
 // A fill to INT8 / INT4 of a neuron whose slot holds its FP16 record (a
 // neuron that fell out of the FP16 tier) is made on the GPU instead: the
@@ -117,17 +119,23 @@ hipError_t launch_fill(const m2c_layer* L, const uint8_t* plan, const uint8_t* c
     src.host[t] = host[t];
     src.stride[t] = t ? L->info.record_stride[t] : 0;
   }
-  // The host link, not the CUs, bounds a fill: 32 workgroups keep 512 KB of
-  // reads in flight, enough for the link's rate. More in flight does not
+  // The host link, not the CUs, bounds a fill of large records: 32 workgroups
+  // keep up to 512 KB of reads in flight (a quarter of that over a record's last
+  // part), enough for the link's rate. More in flight does not
   // speed the fill, and the kernels that overlap it (predictor, select, plan,
   // FFN) wait longer for memory: their requests queue behind the host reads.
   // A stack of 70B layers decodes 9% faster with 32 workgroups than with 64,
   // 15% faster than with 128 (16 and 8 starve the link).
   // Small records leave the link idle at that count (a workgroup has at most
   // one record in flight), so the workgroups double until a mean record each
-  // passes 256 KB, eight-fold at most: d 1024 (mean record 3.6 KB, 128
-  // workgroups) 43 -> 25 us a fill, d 384 (256)
-  // 18 -> 8 us. d 4096 and 8192 stay at 32.
+  // passes 256 KB, eight-fold at most; from d 2432 on they stay at 32. A fill of
+  // d 1024 (mean record 3.6 KB, 128 workgroups) takes 25 us instead of 43, of d 384
+  // (256) 8 instead of 18. On one stream that is a step's gain, with 32 -> with the
+  // rule: d 384 43 -> 36 us, d 1024 59 -> 48, d 2048 (64) 105 -> 89. In a stack of 8
+  // layers on three streams, where the fills run under the other kernels, it costs
+  // some of them: per layer-step d 512 42.2 -> 42.3 us, d 1024 of d_ff 2752 41.8 ->
+  // 42.7 and of 8000 52.8 -> 55.4 (64 workgroups: 52.0), d 1536 50.8 -> 50.8, d 2048
+  // 49.6 -> 51.5.
   if (L->cap <= 0) return hipSuccess;
   const int mean = (L->info.record_stride[1] + L->info.record_stride[2] + L->info.record_stride[3]) / 3;
   int blocks = kFillBlocks;
