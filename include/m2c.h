@@ -143,11 +143,10 @@ typedef struct {
 
 /* m2c_layer_desc.flags */
 enum {
-  /* Sparse FFN by three kernels (up, down by column slices, ordered reduce)
-     whose output is the same bit pattern on every run. The default is two
-     kernels (h of every neuron, then the down projection by column slice and
-     neuron group) whose neuron groups are added into y with fp32 atomics,
-     so the summation order, and the last bits of y, vary from run to run. */
+  /* Sparse FFN at batch 1 by three kernels (up, down by column slices, ordered
+     reduce) whose output is the same bit pattern on every run. By default, and
+     with more rows, groups of neurons are added into y with fp32 atomics, so the
+     summation order, and the last bits of y, vary from run to run. */
   M2C_FLAG_DETERMINISTIC_FFN = 1,
   /* Cache policy variant (Sec. 5.3 "Cache Policy"): a neuron resident at a
      tier at or above the requested one is a HIT and the step uses it at its

@@ -72,9 +72,6 @@ __device__ __forceinline__ float hi_f(uint32_t p) {
   return (float)__builtin_bit_cast(_Float16, (uint16_t)(p >> 16));
 }
 
-static_assert(kFNPR * kFL <= kWorkSlotPad && kFWaves * kFL <= kWorkSlotPad,
-              "slot id reads stay inside the padded work_slot array");
-
 // Unscaled dot products of one 16-byte chunk of INT8 (16 codes) or INT4 (32
 // codes) weights with their x elements (x0, x1 / xq: the chunk's x as it sits
 // in LDS), offset codes as fp16 denormals: sum of (q + 128) x or (q + 8) x,
@@ -229,14 +226,6 @@ __device__ __forceinline__ void h_task(const FTaskArgs& a, const int (&idt)[kFL]
   const int nc8 = d >> 3;
   const uint4* x4 = reinterpret_cast<const uint4*>(x);
   uint4 xv[kXC][2];
-#ifdef M2C_X_FIRST
-#pragma unroll
-  for (int k = 0; k < kXC; ++k) {
-    const int c = tid + k * kFT;
-    xv[k][0] = x4[min(2 * c, nc8 - 1)];
-    xv[k][1] = x4[min(2 * c + 1, nc8 - 1)];
-  }
-#endif
   // unit wu UW + uw of the task sits at table entry (uw / 4) kFNPR + 4 wu + uw % 4
   uint32_t rec[UW];
 #pragma unroll
@@ -261,14 +250,12 @@ __device__ __forceinline__ void h_task(const FTaskArgs& a, const int (&idt)[kFL]
     if (TIER != 3)
       sc[j] = ld2(a.slots + (in ? rec[j / K] + sbase + 2 * ((up ? G : 0) + g) : a.zero));
   }
-#ifndef M2C_X_FIRST
 #pragma unroll
   for (int k = 0; k < kXC; ++k) {
     const int c = tid + k * kFT;
     xv[k][0] = x4[min(2 * c, nc8 - 1)];
     xv[k][1] = x4[min(2 * c + 1, nc8 - 1)];
   }
-#endif
   // x into LDS and the chunk sums of this thread's 16 values, while the
   // records are in flight
   uint4* xs = xlds;
@@ -689,8 +676,7 @@ bool ffn_fused_supported(const m2c_layer* L) {
   return L->desc.d_model <= 8192 && L->arena_bytes < ((int64_t)1 << 32);
 }
 
-int ffn_fused_grid(int d, int cap, int num_cus) {
-  (void)num_cus;
+int ffn_fused_grid(int d, int cap) {
   if (cap <= 0) return 0;
   // h tasks: at most cap / (FP16 neurons per task) + 1 per tier; down tasks:
   // per slice at most cap / (FP16 neurons per run) + 1 per tier

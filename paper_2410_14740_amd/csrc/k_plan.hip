@@ -689,10 +689,8 @@ hipError_t launch_plan(m2c_layer* L, const uint8_t* tier_map, int batch, int ste
 #define M2C_CLASSIFY(P, ONE)                                                                    \
   hipLaunchKernelGGL((plan_classify_kernel<P, ONE>), gc, bc, 0, stream, tier_map, batch, d_ff,   \
                      dom, a.g, a.st)
-  if (L->pools && batch == 1)
+  if (L->pools)  // a layer with pools takes one row (max_batch 1)
     M2C_CLASSIFY(true, true);
-  else if (L->pools)
-    M2C_CLASSIFY(true, false);
   else if (batch == 1)
     M2C_CLASSIFY(false, true);
   else

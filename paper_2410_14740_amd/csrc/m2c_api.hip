@@ -192,8 +192,7 @@ void fill_info_layout(m2c_layer* L) {
   P.work_slot = take(4 * (c + m2c::kWorkSlotPad));
   P.work_mask = take(4 * c);
   P.ffn_tasks = take(m2c::ffn_tasks_used(L)
-                         ? m2c::ffn_task_table_bytes(m2c::ffn_fused_grid(
-                               (int)L->desc.d_model, (int)c, L->num_cus))
+                         ? m2c::ffn_task_table_bytes(m2c::ffn_fused_grid((int)L->desc.d_model, (int)c))
                          : 0);
   P.total_bytes = off;
   I.plan_bytes = off;
@@ -270,7 +269,7 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
       {&p_have, (C + L->S) * 4},
       {&p_stats, 16 * 8},
       {&p_status, 4},
-      {&p_gen, (int64_t)m2c::ffn_fused_grid((int)d, (int)cap, L->num_cus) * 8},
+      {&p_gen, (int64_t)m2c::ffn_fused_grid((int)d, (int)cap) * 8},
       {&p_hw, cap * 8},
   };
   int64_t total = 0;
@@ -314,7 +313,7 @@ m2c_status alloc_device(m2c_layer* L, bool with_bias) {
   L->info.device_bytes = total;
   HIPOK(hipMemset(L->slots + L->map.zero, 0, L->info.slot_bytes), "clear the zero slot");
   HIPOK(hipMemset(L->st.status, 0, 4), "clear the status word");
-  L->ffn_grid = m2c::ffn_fused_grid((int)d, (int)cap, L->num_cus);
+  L->ffn_grid = m2c::ffn_fused_grid((int)d, (int)cap);
   HIPOK(hipMemset(L->st.ffn_gen, 0, (size_t)(L->ffn_grid > 0 ? L->ffn_grid : 1) * 8),
         "clear the FFN workgroup counters");
   HIPOK(hipMemset(L->st.ffn_hw, 0, (size_t)(cap > 0 ? cap : 1) * 8), "clear the FFN h words");

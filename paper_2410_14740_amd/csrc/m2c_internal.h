@@ -13,9 +13,9 @@ namespace m2c {
 // m2c_layer_stats.
 constexpr int M2C_STATUS_PLAN_OVERFLOW = 2;  // a tier map had more active neurons than cap
 constexpr int M2C_STATUS_FFN_WAIT = 4;      // a sparse FFN gave up waiting for an h value
-// Spare entries after the plan's work_slot array: the FFN kernels read slot
-// ids in wave-uniform blocks (groups of four at batch 1, a whole run of up to
-// 512 items in the batched down projection) that may run past the last item.
+// Spare entries after the plan's work_slot array: the batched FFN reads slot
+// ids past the last item, in whole tiles (up to 32 items) and whole steps of 32,
+// one step ahead. The number is part of the plan's layout in m2c.h.
 constexpr int kWorkSlotPad = 512;
 
 // ---------------------------------------------------------------------------
@@ -162,7 +162,7 @@ hipError_t launch_ffn_batch(m2c_layer* L, const uint16_t* x, int batch, const ui
 hipError_t launch_ffn_split(m2c_layer* L, const uint16_t* x, const uint8_t* plan, float* y,
                             hipStream_t stream);
 bool ffn_fused_supported(const m2c_layer* L);
-int ffn_fused_grid(int d_model, int cap, int num_cus);  // workgroups (and gen counters) of the one-launch FFN
+int ffn_fused_grid(int d_model, int cap);  // workgroups (and gen counters) of the one-launch FFN
 // The one-launch FFN's task table in a plan: whether the layer's plans carry
 // one (batch-1 FFN calls use that kernel) and its bytes for a grid.
 bool ffn_tasks_used(const m2c_layer* L);
@@ -181,37 +181,6 @@ __device__ __forceinline__ float h2f(uint16_t b) {
 __device__ __forceinline__ uint32_t score_key(float f) {
   uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// Block-wide exclusive prefix sum over one value per thread (at most 1024
-// threads). `tmp` holds at least blockDim.x / 64 entries of shared memory.
-// Returns the exclusive prefix; *total gets the block sum. Each wave scans
-// its lanes, then (after one barrier) the wave totals itself, lane q holding
-// wave q's total, so no single thread walks the totals. Contains
-// __syncthreads() (the second lets the caller reuse `tmp`).
-template <typename T>
-__device__ T block_exclusive_scan(T v, T* tmp, T* total) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int nwaves = (blockDim.x + 63) >> 6;
-  T incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    T o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
-  if (lane == 63) tmp[wave] = incl;
-  __syncthreads();
-  T wt = lane < nwaves ? tmp[lane] : T(0);
-#pragma unroll
-  for (int off = 1; off < 16; off <<= 1) {
-    T o = __shfl_up(wt, off);
-    if (lane >= off) wt += o;
-  }
-  const T before = wave > 0 ? __shfl(wt, wave - 1) : T(0);
-  *total = __shfl(wt, nwaves - 1);
-  __syncthreads();
-  return before + incl - v;
 }
 
 }  // namespace m2c
