@@ -38,8 +38,10 @@ def scores_of(kind, n, rng):
 KINDS = ("normal", "ties", "zeros", "outlier", "nonfinite", "tiny", "equal", "crowded", "halves")
 
 
-# d_ff at the edges of the register instances, and above the widest (rows read again by each pass)
-@pytest.mark.parametrize("d_ff", [1, 63, 1024, 1025, 4096, 11008, 28673, 40960, 40961])
+# d_ff in each register instance (1, 2, 4, 8, 12, .. 32, 40 scores per thread: both sides of the
+# narrow ones' edges, the upper edge of the others), and above the widest (rows read again by each pass)
+@pytest.mark.parametrize("d_ff", [1, 63, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 11008, 16384, 20480,
+                                  24576, 28672, 28673, 32769, 40960, 40961, 70000])
 def test_select_scores(d_ff):
     from paper_2410_14740_amd import m2c
     d, r = 128, 8
