@@ -496,12 +496,13 @@ __global__ __launch_bounds__(kBHThreads) void ffn_bh_kernel(
 // shape) and on empty workgroups of a grid sized for the plan's capacity.
 // Measured (MI355X, rocprofv3 kernel time, before -> now): 70B shape at 32 rows
 // 105 -> 41.9 us, 7B at 8 / 17 / 32 rows 11.8 / 28.9 / 36.0 -> 10.7 / 17.0 / 20.8.
-// What it costs: its registers leave two waves per SIMD, and a run's second step
-// waits for a memory round trip of its own, where the runs before had five waves
-// and all of a run in flight. With 2 to 8 rows and two or more steps per wave that
-// shows: a call at d 1536 of d_ff 20000 with 4 rows 20.2 -> 21.2 us, d 1024 of
-// 30000 18.9 -> 19.8, d 2048 of 11008 17.4 -> 18.1. Three waves per SIMD (168
-// registers) spill 222 values: 7B at 8 rows 25.8 -> 46.8 us a call.
+// What it costs: a wave's second step waits for a memory round trip of its own,
+// where the runs before had all of a run in flight. With 2 to 8 rows and two or more
+// steps per wave that shows: a call at d 1536 of d_ff 20000 with 4 rows 20.2 -> 21.2
+// us, d 1024 of 30000 18.9 -> 19.7, d 2048 of 11008 17.4 -> 18.2. One step per wave
+// needs three waves per SIMD and twice the workgroups' atomics: 21.4 us for the 21.2
+// (both parts of h in one matrix tile, 168 registers); without that tile 168
+// registers spill 222 values.
 
 constexpr int kDMThreads = 256;
 constexpr int kDMWaves = kDMThreads / 64;
